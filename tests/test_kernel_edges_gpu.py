@@ -1,0 +1,55 @@
+"""Kernels at the edges of their tiles and dispatch ranges, against the FP64 reference of each."""
+import numpy as np
+import pytest
+
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2412_02413_amd import nn, pam
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pam._lib()
+    return torch, nn
+
+
+def bf16(torch, a):
+    """The array rounded to BF16, as FP64 and as a device tensor."""
+    t = torch.tensor(a, dtype=torch.float32).to(torch.bfloat16)
+    return t.double().numpy(), t.cuda()
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+# The products of BF16 values are exact in FP32 and n of them are summed in FP32 in some order: each
+# addition rounds by at most 2^-24 of the partial sum, so by about 2^-24 sqrt(n) of the result's own
+# size in a random walk; 1e-6 holds up to n = 250 times over that.
+@pytest.mark.parametrize("B,h,w,c_in,c_out,bias", [
+    (1, 1, 1, 32, 32, True),         # one pixel: every other pixel of the tile is outside
+    (2, 8, 32, 32, 32, True),        # exactly one tile per image
+    (1, 9, 33, 64, 32, False),       # a remainder of one row and one column, no bias gradient
+    (3, 7, 31, 32, 64, True),        # one short of a tile in both directions
+    (8, 64, 32, 256, 256, True),     # the deepest layer: 64 channel pairs, four runs of tiles
+])
+def test_conv3x3_wgrad_tile_edges(env, B, h, w, c_in, c_out, bias):
+    torch, nn = env
+    rng = np.random.default_rng(h * w + c_in)
+    x, xd = bf16(torch, rng.standard_normal((B, h, w, c_in)))
+    dy, dyd = bf16(torch, rng.standard_normal((B, h, w, c_out)))
+    dw0 = rng.standard_normal((9, c_in, c_out)).astype(np.float32)
+    dw = torch.tensor(dw0, device="cuda")                 # the gradients add to what is there
+    db = torch.zeros(c_out, device="cuda") if bias else None
+    nn.conv3x3_wgrad(xd, c_in, dyd, c_out, B, h, w, c_in, c_out, dw, db)
+    torch.cuda.synchronize()
+    xp = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    want = np.stack([xp[:, t // 3: t // 3 + h, t % 3: t % 3 + w].reshape(-1, c_in).T @ dy.reshape(-1, c_out)
+                     for t in range(9)]) + dw0
+    e = rel(dw.cpu().numpy().astype(np.float64), want)
+    print(f"dW rel L2 {e:.2e}", flush=True)
+    assert e < 1e-6
+    if bias:
+        assert rel(db.cpu().numpy().astype(np.float64), dy.sum((0, 1, 2))) < 1e-6
