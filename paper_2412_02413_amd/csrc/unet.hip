@@ -357,6 +357,22 @@ __global__ void relu_bwd_kernel(const bf16* y, int32_t ldy, bf16* dy, int32_t ld
   if (!((float)y[p * ldy + k] > 0.f)) dy[p * lddy + k] = (bf16)0.f;
 }
 
+// The same on 8 channels (16 bytes) per thread: bound by reading y and dy and writing dy.  Two-byte accesses took
+// 60 us at 8 x 512 x 256 x 32, this 29 us (7 TB/s counting both reads and the write: much of dy is
+// still in the last-level cache).
+__global__ void relu8_bwd_kernel(const bf16* y, int32_t ldy, bf16* dy, int32_t lddy, int64_t n8, int32_t c8) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n8) return;  // n8 = pixels * c / 8
+  const int64_t p = e / c8;
+  const int k = (int)(e - p * c8) * 8;
+  const v8bf v = *reinterpret_cast<const v8bf*>(y + p * ldy + k);
+  v8bf* d = reinterpret_cast<v8bf*>(dy + p * lddy + k);
+  v8bf g = *d;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) g[j] = (float)v[j] > 0.f ? g[j] : (bf16)0.f;
+  *d = g;
+}
+
 __global__ void maxpool_kernel(const bf16* x, int32_t ldx, int64_t n, int32_t h, int32_t w, int32_t c, bf16* y,
                                int32_t ldy, uint8_t* arg) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -917,8 +933,13 @@ pam_status_t pam_nn_relu_backward(const void* y, int32_t ldy, void* dy, int32_t 
                                   void* hip_stream) {
   if (!y || !dy || pixels < 1 || c < 1 || ldy < c || lddy < c) return PAM_ERR_INVALID_ARG;
   const int64_t n = pixels * c;
-  hipLaunchKernelGGL(relu_bwd_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
-                     static_cast<const bf16*>(y), ldy, static_cast<bf16*>(dy), lddy, n, c);
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if (vec8(c, ldy, lddy, y, dy))
+    hipLaunchKernelGGL(relu8_bwd_kernel, dim3(blocks_for(n / 8, 256)), dim3(256), 0, st, static_cast<const bf16*>(y),
+                       ldy, static_cast<bf16*>(dy), lddy, n / 8, c / 8);
+  else
+    hipLaunchKernelGGL(relu_bwd_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, static_cast<const bf16*>(y), ldy,
+                       static_cast<bf16*>(dy), lddy, n, c);
   return launched();
 }
 

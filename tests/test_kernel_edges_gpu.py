@@ -53,3 +53,18 @@ def test_conv3x3_wgrad_tile_edges(env, B, h, w, c_in, c_out, bias):
     assert e < 1e-6
     if bias:
         assert rel(db.cpu().numpy().astype(np.float64), dy.sum((0, 1, 2))) < 1e-6
+
+
+@pytest.mark.parametrize("pixels,c,pad", [(1, 8, 0), (257, 32, 64), (33, 24, 8), (100, 12, 4), (64, 8, 4)])
+def test_relu_backward_forms(env, pixels, c, pad):
+    """Eight channels per thread where c and both strides are multiples of 8, else one: the values
+    kept and those cleared are exact, and nothing outside the c channels changes."""
+    torch, nn = env
+    rng = np.random.default_rng(pixels + c)
+    y, yd = bf16(torch, rng.standard_normal((pixels, c + pad)))
+    y[0, 0], yd[0, 0] = 0.0, 0.0
+    dy, dyd = bf16(torch, rng.standard_normal((pixels, c + pad)))
+    nn.relu_backward(yd, c + pad, dyd, c + pad, pixels, c)
+    want = dy.copy()
+    want[:, :c] *= y[:, :c] > 0
+    np.testing.assert_array_equal(dyd.double().cpu().numpy(), want)
