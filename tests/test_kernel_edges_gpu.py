@@ -68,3 +68,40 @@ def test_relu_backward_forms(env, pixels, c, pad):
     want = dy.copy()
     want[:, :c] *= y[:, :c] > 0
     np.testing.assert_array_equal(dyd.double().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("pixels,c", [(1, 8), (1000, 24), (262145, 32), (70, 120), (300, 12)])
+def test_head_forms(env, pixels, c):
+    """The head's loss and gradients at the edges of its pixel loops (one pixel; one past 256
+    workgroups of 1024) and of its channel groups (1, 3, 4, 15 of 8; 12 channels take the other
+    form).  Sums of n terms in FP32 in some order: 2^-24 sqrt(n) of the largest partial sum, so 1e-4
+    of the loss and of a gradient's norm covers cancellation; the BF16 output rounds by 2^-9."""
+    torch, nn = env
+    rng = np.random.default_rng(c + pixels)
+    f, fd = bf16(torch, rng.standard_normal((pixels, c)))
+    w = (rng.standard_normal((c, 2)) / np.sqrt(c)).astype(np.float32)
+    b = np.float32([0.1, -0.2])
+    t = rng.uniform(0, 1, pixels).astype(np.float32)
+    wt = (rng.uniform(0.5, 1.5, pixels) / pixels).astype(np.float32)
+    dev = [torch.tensor(a, device="cuda") for a in (w, b, t, wt)]
+    mask, err = torch.empty(pixels, device="cuda"), torch.empty(pixels, device="cuda")
+    dz, loss = torch.empty((pixels, 2), device="cuda"), torch.zeros(3, device="cuda")
+    nn.head(fd, c, pixels, dev[0], dev[1], dev[2], dev[3], mask, err, dz, loss, pixels)
+    df = torch.empty((pixels, c), dtype=torch.bfloat16, device="cuda")
+    dw, db = torch.zeros((c, 2), device="cuda"), torch.zeros(2, device="cuda")
+    nn.head_backward(fd, c, pixels, dev[0], dz, df, dw, db)
+    plain = torch.empty(pixels, device="cuda")
+    nn.head(fd, c, pixels, dev[0], dev[1], None, None, plain, err, None, None, pixels)
+    assert torch.equal(plain, mask)
+    z = f @ w.astype(np.float64) + b
+    m, e = 1 / (1 + np.exp(-z.T))
+    ae = np.abs(m - t)
+    lz = np.logaddexp(0, z)
+    want = [np.sum(wt * (t * (lz[:, 0] - z[:, 0]) + (1 - t) * lz[:, 0])),
+            np.sum(wt * (ae * (lz[:, 1] - z[:, 1]) + (1 - ae) * lz[:, 1])), np.sum(wt * ae)]
+    np.testing.assert_allclose(loss.cpu().numpy(), want, rtol=1e-4)
+    g = np.stack([(m - t) * wt, (e - ae) * wt], 1)
+    assert rel(dz.double().cpu().numpy(), g) < 1e-5
+    assert rel(dw.double().cpu().numpy(), f.T @ g) < 1e-4
+    assert rel(db.double().cpu().numpy(), g.sum(0)) < 1e-4
+    assert rel(df.double().cpu().numpy(), g @ w.astype(np.float64).T) < 2 ** -8
