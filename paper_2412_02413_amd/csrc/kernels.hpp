@@ -539,50 +539,86 @@ struct K4Args {
   double eps;
 };
 
-__global__ __launch_bounds__(256) void k4_weight(K4Args a) {
-  __shared__ float red[256];
+// 1 / sqrt(x) in FP64 for x > 0 (one Newton step on the hardware's estimate of about 2^-26: 2^-50; 0 for infinity).
+__device__ __forceinline__ double rsqrt_pos(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  return x < __builtin_huge_val() ? fma(0.5 * y, fma(-x * y, y, 1.0), y) : 0.0;
+}
+
+// cbrt(a) for 0 < a <= 1 in FP64, accurate to about 1e-12: one Newton step of t <- t (4 - a t^3) / 3 for
+// t = a^(-1/3) from the FP32 hardware log2 / exp2, then a t^2.  Values whose FP32 image is not normal take cbrt().
+__device__ __forceinline__ double cbrt_unit(double a) {
+  if (!(a > 1e-36)) return cbrt(a);
+  const double t = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)a) * (-1.0f / 3.0f));
+  const double e = fma(-a * t, t * t, 1.0);          // 1 - a t^3
+  const double u = fma(t * (1.0 / 3.0), e, t);
+  return a * u * u;
+}
+
+// The bin splits' partial sums of a pixel added in FP64, then NCC, weight and energy.  A workgroup covers 256 pixels
+// of one frame with SG threads a pixel: thread group sg adds splits sg, sg + SG, ... of every channel and the groups
+// meet in LDS, so that many splits are not one serial chain of loads.  Bound by reading the partial sums (at 64 frames
+// of one split also by the FP64 arithmetic, hence the Newton forms above).  One thread a pixel with run-time channel
+// loops and library sqrt, division and cbrt took 42 us for 19,328 pixels of 26 splits (now 5.0), 31 us for 131,072 of
+// 16 (now 10.5: 50 MB at 4.8 TB/s) and 98 us for 64 frames of 131,072 of one split (now 54: 268 MB at 5.0 TB/s).
+template <int NSUB, int SG>
+__global__ __launch_bounds__(256 * SG) void k4_weight(K4Args a) {
+  constexpr int NP = AccCount<NSUB>::pairs, NR = AccCount<NSUB>::total;   // pairs and channels read here
+  __shared__ double part[SG > 1 ? SG - 1 : 1][NR][SG > 1 ? 256 : 1];
+  __shared__ float red[4];
   const int f = blockIdx.y;
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  const int na = a.n_acc;                                        // channel stride
-  const int nr = a.n_sub == 3 ? 6 : (a.n_sub == 2 ? 3 : 1);     // channels read here
-  float wv = 0.f;
+  const int t = threadIdx.x & 255, sg = threadIdx.x >> 8;
+  const int p = blockIdx.x * 256 + t;
+  double v[NR];
+#pragma unroll
+  for (int c = 0; c < NR; ++c) v[c] = 0.0;
   if (p < a.pix) {
-    double v[6] = {0, 0, 0, 0, 0, 0};
-    for (int s = 0; s < a.n_split; ++s) {
-      const float* src = a.accum + ((size_t)s * a.F + f) * na * a.pix + p;
-      for (int c = 0; c < nr; ++c) v[c] += (double)src[(size_t)c * a.pix];
+    const float* src = a.accum + (size_t)f * a.n_acc * a.pix + p;
+    const size_t plane = (size_t)a.F * a.n_acc * a.pix;                   // one split
+#pragma unroll 4
+    for (int s = sg; s < a.n_split; s += SG)
+#pragma unroll
+      for (int c = 0; c < NR; ++c) v[c] += (double)src[s * plane + (size_t)c * a.pix];
+  }
+  if constexpr (SG > 1) {
+    if (sg > 0) {
+#pragma unroll
+      for (int c = 0; c < NR; ++c) part[sg - 1][c][t] = v[c];
     }
-    double E, w;
-    if (a.n_sub == 1) {
-      E = v[0];
-      w = 1.0;
-    } else {
-      const int np = a.n_sub == 3 ? 3 : 1;
-      const int pi_[3] = {0, 1, 2}, pj_[3] = {1, 2, 0};
-      double prod = 1.0, esum = 0.0;
-      for (int i = 0; i < a.n_sub; ++i) esum += v[i];
-      for (int q = 0; q < np; ++q) {
-        const double cc = v[a.n_sub + q];
-        esum += 2.0 * cc;
-        const double den = sqrt(v[pi_[q]]) * sqrt(v[pj_[q]]);
-        const double r = den > 0.0 ? cc / den : 0.0;
-        if (a.rho_pairs) a.rho_pairs[((size_t)f * np + q) * a.pix + p] = (float)r;
-        prod *= fmin(1.0, fmax(a.eps, r));
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SG - 1; ++k)
+#pragma unroll
+      for (int c = 0; c < NR; ++c) v[c] += part[k][c][t];
+  }
+  float wv = 0.f;
+  if (sg == 0 && p < a.pix) {
+    double E = 0.0, w = 1.0;
+#pragma unroll
+    for (int i = 0; i < NSUB; ++i) E += v[i];
+    if constexpr (NSUB > 1) {
+      constexpr int pi_[3] = {0, 1, 2}, pj_[3] = {1, 2, 0};
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const double cc = v[NSUB + q];
+        E += 2.0 * cc;
+        const double den2 = v[pi_[q]] * v[pj_[q]];                       // FP32-range sums: in range
+        const double r = den2 > 0.0 ? cc * rsqrt_pos(den2) : 0.0;
+        if (a.rho_pairs) a.rho_pairs[((size_t)f * NP + q) * a.pix + p] = (float)r;
+        w *= fmin(1.0, fmax(a.eps, r));
       }
-      E = esum;
-      w = (a.n_sub == 3) ? cbrt(prod) : prod;
+      if constexpr (NSUB == 3) w = cbrt_unit(w);
     }
     a.energy[(size_t)f * a.pix + p] = (float)E;
     a.weight[(size_t)f * a.pix + p] = (float)w;
     wv = (float)w;
   }
-  red[threadIdx.x] = wv;
+  // the workgroup's largest weight (group 0: four waves)
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) wv = fmaxf(wv, __shfl_xor(wv, o));
+  if (sg == 0 && (t & 63) == 0) red[t >> 6] = wv;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + st]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.blockmax[(size_t)f * a.n_blk + blockIdx.x] = red[0];
+  if (threadIdx.x == 0) a.blockmax[(size_t)f * a.n_blk + blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
 __global__ __launch_bounds__(256) void k4_image(K4Args a) {

@@ -2,6 +2,8 @@
 import numpy as np
 import pytest
 
+from paper_2412_02413_amd import synth
+
 
 pytestmark = pytest.mark.gpu
 
@@ -105,3 +107,37 @@ def test_head_forms(env, pixels, c):
     assert rel(dw.double().cpu().numpy(), f.T @ g) < 1e-4
     assert rel(db.double().cpu().numpy(), g.sum(0)) < 1e-4
     assert rel(df.double().cpu().numpy(), g @ w.astype(np.float64).T) < 2 ** -8
+
+
+# FP32 outputs of FP64 arithmetic on the same FP32 partial sums: one rounding (2^-24) besides the
+# 1e-12 of the Newton forms.
+@pytest.mark.parametrize("n_sub,eps,frames", [(3, 1e-3, 1), (3, 1e-20, 1), (3, 1e-3, 24), (2, 1e-3, 1), (1, 1e-3, 2)])
+def test_weight_and_energy_from_partial_sums(env, n_sub, eps, frames):
+    """NCC, weight and energy against their definition on the call's own partial sums: one frame
+    (many bin splits) and 24 (few), a clamp so low that the cube root leaves the FP32 range."""
+    torch, _ = env
+    from paper_2412_02413_amd import pam
+    g = synth.cfg1_geometry().replace(n_sub=n_sub, eps=eps)
+    rf = synth.batch(synth.cfg1_frame, list(range(40, 40 + frames)))
+    plan = pam.pam_plan(g, 0, "fp32")
+    try:
+        out = pam.reconstruct(plan, torch.from_numpy(rf).cuda())
+        torch.cuda.synchronize()
+        lay = pam.pam_workspace_layout(plan, frames, g.n_samples)
+    finally:
+        pam.pam_destroy(plan)
+    pix = g.n_z * g.n_x
+
+    def view(offset, n):
+        return out["workspace"][offset: offset + 4 * n].cpu().numpy().view(np.float32).astype(np.float64)
+
+    acc = view(lay.accum, lay.n_split * frames * lay.n_acc * pix).reshape(lay.n_split, frames, lay.n_acc, pix).sum(0)
+    S, C = acc[:, :n_sub], acc[:, n_sub:]
+    E, w = S.sum(1) + 2 * C.sum(1), np.ones((frames, pix))
+    for q, (i, j) in enumerate({1: [], 2: [(0, 1)], 3: [(0, 1), (1, 2), (2, 0)]}[n_sub]):
+        den = np.sqrt(S[:, i]) * np.sqrt(S[:, j])
+        w *= np.clip(np.where(den > 0, C[:, q] / np.where(den > 0, den, 1), 0), eps, 1)
+    w = np.cbrt(w) if n_sub == 3 else w
+    print(f"{lay.n_split} splits, smallest weight {w.min():.1e}", flush=True)
+    np.testing.assert_allclose(view(lay.weight, frames * pix).reshape(frames, pix), w, rtol=2.0 ** -23)
+    np.testing.assert_allclose(view(lay.energy, frames * pix).reshape(frames, pix), E, rtol=2.0 ** -23)
