@@ -19,6 +19,7 @@
 // transforms are radix-4 FFTs in registers (about 10 operations per point and stage,
 // against 8 L per point for the direct sum).
 #pragma once
+#include "dft_small.hpp"
 #include "kernels.hpp"
 
 namespace pam {
@@ -122,10 +123,11 @@ __device__ __forceinline__ void dft32s(float2* v) {
   for (int k = 0; k < 32; ++k) v[k] = out[k];
 }
 template <int S, int R>
-__device__ __forceinline__ void dftn(float2* v) {
+__device__ __forceinline__ void dftn(float2 (&v)[R]) {
   if constexpr (R == 8) dft8s<S>(v);
   else if constexpr (R == 16) dft16s<S>(v);
-  else dft32s<S>(v);
+  else if constexpr (R == 32) dft32s<S>(v);
+  else dft_small<S, R>(v);
 }
 
 template <int NSUB, int N2>

@@ -34,12 +34,10 @@
 // q' = 16 q1 + q2, coefficient q = 32 q1 + 2 q2 + e sits in staged row 2 q2 + e.
 //
 // Matrix-core operand layouts (lane l, h = l / 32, c = l % 32):
-//   v_mfma_f32_32x32x2_f32:        A[c][2t + h],  B[2t + h][c],  t = 0..15 (k-steps)
 //   v_mfma_f32_32x32x16_{bf16,f16}: A[c][16s + 8h + j], B[16s + 8h + j][c], s = 0..1, j = 0..7
 //   result, register v = 0..15:     C[8(v/4) + 4h + v%4][c]
-// K index <-> (input index m, re/im): FP32 k = 2t + h <-> m = 8h + t/2, re/im = t%2;
-// 16-bit k = 16s + 8h + j <-> m = 8h + 4s + j/2, re/im = j%2.  Either way lane half h
-// supplies the inputs m = 8h..8h+7 of its column, re and im.  Output rows are
+// K index <-> (input index m, re/im): k = 16s + 8h + j <-> m = 8h + 4s + j/2, re/im = j%2,
+// so lane half h supplies the inputs m = 8h..8h+7 of its column, re and im.  Output rows are
 // (x, re/im) = x + 16 (re/im), so register v < 8 holds Re and v + 8 Im of output
 // x = 8(v/4) + 4h + v%4.
 #pragma once
@@ -196,8 +194,7 @@ __device__ __forceinline__ void ff_store(const K3Args& a, int sp, int f, int d0,
 }
 
 // ---------------------------------------------------------------------------
-// The kernel.  T = float: FP32 operands on v_mfma_f32_32x32x2_f32.  T = __bf16 or
-// _Float16: operands on v_mfma_f32_32x32x16_*, each split into hi = T(x) and
+// The kernel.  T = __bf16 or _Float16: operands on v_mfma_f32_32x32x16_*, each split into hi = T(x) and
 // lo = T(x - hi); PASSES = 3 sums hi.hi + hi.lo + lo.hi, PASSES = 1 takes hi.hi.
 //
 // Per bin a wave runs a front half (propagator, stage-1 operands, stage-1
@@ -209,7 +206,7 @@ __device__ __forceinline__ void ff_store(const K3Args& a, int sp, int f, int d0,
 //
 // Scale: for FP16 operands K2 scales each bin's coefficients by a power of two s and
 // the twiddles carry 1/16, so that both stages' operands stay in FP16 range; 16/s
-// then multiplies the fields in the fold.  FP32 and BF16 operands take s = 1 and
+// then multiplies the fields in the fold.  BF16 operands take s = 1 and
 // unscaled twiddles.
 // ---------------------------------------------------------------------------
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -242,10 +239,9 @@ template <typename T, int PASSES, int NSUB, bool COH = false, int R = 1>
 __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
   static_assert(!COH || (NSUB == 1 && R == 1), "pair cross-spectra come with the full-aperture sums at N = 256");
   static_assert(R == 1 || R == 2, "N = 256 or 512");
-  constexpr bool F32 = std::is_same<T, float>::value;
   constexpr bool SCALED = std::is_same<T, _Float16>::value;   // keep K2's scale through stage 3
   constexpr int NP = AccCount<NSUB>::pairs;
-  typedef typename std::conditional<F32, float, typename Mma<typename std::conditional<F32, __bf16, T>::type>::v8>::type v8;
+  typedef typename Mma<T>::v8 v8;
   extern __shared__ float2 lds2[];
   float2* stage = lds2;                                          // [2][ff_stage_f2<NSUB, R>]
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -266,19 +262,8 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
   const bool lag = w >= 4;
 
   // constant 16-point DFT operands
-  float W32[16];
   v8 Wh[2], Wl[2];
-  if constexpr (F32) {
-    const float4* src = reinterpret_cast<const float4*>(a.ff_w32) + lane * 4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float4 q = src[k];
-      W32[4 * k] = q.x;
-      W32[4 * k + 1] = q.y;
-      W32[4 * k + 2] = q.z;
-      W32[4 * k + 3] = q.w;
-    }
-  } else {
+  {
     const uint4* src = reinterpret_cast<const uint4*>(a.ff_w16) + lane * 4;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -303,42 +288,28 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
   }
 
   // products of one stage: C_i = W x operand_i for every sub-aperture
-  auto gemm = [&](const float (&bf)[NSUB][16], const v8 (&bh)[NSUB][2], const v8 (&bl)[NSUB][2],
-                  v16f (&C)[NSUB]) {
+  auto gemm = [&](const v8 (&bh)[NSUB][2], const v8 (&bl)[NSUB][2], v16f (&C)[NSUB]) {
     // the first product of each chain takes a zero accumulator (an inline constant)
     const v16f zero = {};
-    if constexpr (F32) {
 #pragma unroll
-      for (int t = 0; t < 16; ++t)
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int i = 0; i < NSUB; ++i)
-          C[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(W32[t], bf[i][t], t == 0 ? zero : C[i], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int i = 0; i < NSUB; ++i) {
-          C[i] = Mma<T>::run(Wh[s], bh[i][s], s == 0 ? zero : C[i]);
-          if (PASSES == 3) {
-            C[i] = Mma<T>::run(Wh[s], bl[i][s], C[i]);
-            C[i] = Mma<T>::run(Wl[s], bh[i][s], C[i]);
-          }
+      for (int i = 0; i < NSUB; ++i) {
+        C[i] = Mma<T>::run(Wh[s], bh[i][s], s == 0 ? zero : C[i]);
+        if (PASSES == 3) {
+          C[i] = Mma<T>::run(Wh[s], bl[i][s], C[i]);
+          C[i] = Mma<T>::run(Wl[s], bh[i][s], C[i]);
         }
-    }
+      }
   };
   // 16 operand values (inputs m = 8h..8h+7, re/im) of sub-aperture i into the operand registers
-  auto put = [&](int i, const float (&x)[16], float (&bf)[NSUB][16], v8 (&bh)[NSUB][2], v8 (&bl)[NSUB][2]) {
-    if constexpr (F32) {
+  auto put = [&](int i, const float (&x)[16], v8 (&bh)[NSUB][2], v8 (&bl)[NSUB][2]) {
 #pragma unroll
-      for (int t = 0; t < 16; ++t) bf[i][t] = x[t];
-    } else {
+    for (int s = 0; s < 2; ++s) {
+      float y[8];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        float y[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) y[j] = x[8 * s + j];
-        FfOps<T>::split(y, bh[i][s], bl[i][s]);
-      }
+      for (int j = 0; j < 8; ++j) y[j] = x[8 * s + j];
+      FfOps<T>::split(y, bh[i][s], bl[i][s]);
     }
   };
 
@@ -361,7 +332,6 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
       for (int m = 0; m < 8; ++m)
         if (kzr[m] < 0.0) H[m] = propagator(z, kzr[m], a.zero_evanescent);
     }
-    float bf[NSUB][16];
     v8 bh[NSUB][2], bl[NSUB][2];
 #pragma unroll
     for (int i = 0; i < NSUB; ++i) {
@@ -377,10 +347,10 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
         x[4 * k + 2] = a1.x;
         x[4 * k + 3] = a1.y;
       }
-      put(i, x, bf, bh, bl);
+      put(i, x, bh, bl);
     }
     v16f C[NSUB];
-    gemm(bf, bh, bl, C);
+    gemm(bh, bl, C);
 #pragma unroll
     for (int i = 0; i < NSUB; ++i)
 #pragma unroll
@@ -393,7 +363,6 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
 
   // back half of bin b: stage-3 operands from the transpose buffer, products, fold
   auto back = [&](int b) {
-    float bf[NSUB][16];
     v8 bh[NSUB][2], bl[NSUB][2];
 #pragma unroll
     for (int i = 0; i < NSUB; ++i) {
@@ -407,10 +376,10 @@ __global__ __launch_bounds__(512, 1) void k3ff(K3Args a0, K3Groups grp) {
         x[4 * k + 2] = yy.z;
         x[4 * k + 3] = yy.w;
       }
-      put(i, x, bf, bh, bl);
+      put(i, x, bh, bl);
     }
     v16f C[NSUB];
-    gemm(bf, bh, bl, C);
+    gemm(bh, bl, C);
     const float inv = SCALED ? 16.0f * a.inv_scale[(size_t)f * a.n_sel + b] : 1.0f;
 #pragma unroll
     for (int v = 0; v < 8; ++v) {

@@ -1,5 +1,5 @@
-// K3 for FP32 operands at N = 128, 256 and 512: the inverse lateral transform as a 16 x N/16
-// FFT on the vector ALUs.
+// K3 for FP32 operands, every lateral size N = 32 .. 512 in steps of 32: the inverse lateral
+// transform as a 16 x N/16 FFT on the vector ALUs.
 //
 // Same factorisation as k3_factored.hpp (q = (N/16) q1 + q2, x = x1 + 16 x2):
 //   stage 1  Y(x1, q2)  = sum_q1 A((N/16) q1 + q2) e^{2 pi i q1 x1 / 16}
@@ -24,20 +24,30 @@
 // With COH (n_sub = 1) the adjacent-pixel pair sums come from lanes j ^ 1 (column
 // partner) and g ^ 1, i.e. lane ^ 16 (depth partner).
 //
-// N = 128.  A group holds two depths: in stage 1 lane j is (depth j / 8, column q2 = j % 8)
-// and reads staged row q2 (8 rows), so the transpose block row x1 holds both depths' eight
-// q2 values; in stage 3 lane j = x1 runs two 8-point FFTs, one per depth, and its 16
-// pixels are (depth d, x = j + 16 x2) for d = 0, 1 and x2 = 0..7.  A wave holds eight
-// depths and a workgroup 32.
+// Other N <= 256: stage 3 has K = N / 16 < 16 points (dft_small.hpp, codelets at 8 and 16).
+// A group then holds DG depths of CW = 16 / DG >= K stage-1 columns each: lane j is (depth
+// j / CW, column q2 = j % CW), columns K .. CW - 1 idle; in stage 3 lane j = x1 runs DG
+// transforms of K points, one per depth, and its pixels are (depth d, x = j + 16 x2), d < DG,
+// x2 < K.  N = 128: two depths of 8 columns, 192: one of 12, 96: two of 6, 64: four of 4.
+// A wave holds 4 DG depths and a workgroup 16 DG.
 //
-// N = 512 splits the sum by the parity e of q as k3ff does:
-// p(x) = P_0(x mod 256) + e^{2 pi i x / 512} P_1(x mod 256), P_e the 256-point transform of
-// A(2 q' + e).  The lane groups of a wave become (depth, e) = (g / 2, g % 2), so a wave holds
-// two depths and a workgroup eight.  Lane (g, j) takes its inputs from staged row 2 j + e
-// (q = 32 m + 2 j + e, K2's order for N / 16 = 32 rows); after stage 3 the lanes g and g ^ 1
-// (lane ^ 16) exchange P_0 and P_1 of their 16 columns x' = j + 16 x2, and group e forms
-// pixel x' + 256 e as P_0 +- w P_1 with w = e^{2 pi i x' / 512} (a 16 x 16 table in LDS).
+// N > 256 splits the sum by the parity e of q as k3ff does:
+// p(x) = P_0(x mod N/2) + e^{2 pi i x / N} P_1(x mod N/2), P_e the transform of A(2 q' + e)
+// over N/2 = 16 K points (K = 16 at N = 512, 12 at 384, ...).  The lane groups of a wave
+// become (depth, e) = (g / 2, g % 2), so a wave holds two depths and a workgroup eight.  Lane
+// (g, j) takes its inputs from staged row 2 j + e (q = 2 K m + 2 j + e, K2's order for
+// N / 16 = 2 K rows); after stage 3 the lanes g and g ^ 1 (lane ^ 16) exchange P_0 and P_1 of
+// their columns x' = j + 16 x2, and group e forms pixel x' + e N/2 as P_0 +- w P_1 with
+// w = e^{2 pi i x' / N} (a K x 16 table in LDS).
+//
+// The sizes without a codelet ran as dense DFT-GEMMs on the FP32 matrix cores before (4 N
+// flops per complex output against about 11 operations per point and stage): 4.14 -> 0.58 ms for
+// 4 frames of 301 x 192 pixels and 691 bins (43 TFLOP/s of the method's operations; the
+// idle stage-1 lanes, 4 of 16 here, are what it lacks to the 61 of N = 256).
 #pragma once
+#include <utility>
+
+#include "dft_small.hpp"
 #include "k3_factored.hpp"
 
 namespace pam {
@@ -45,26 +55,36 @@ namespace pam {
 constexpr int kFtWaves = 4;                    // waves per workgroup
 constexpr int kFtTr = 16 * kFfRow;             // float2 per lane group's transpose block [16 x1][kFfRow]
 
-// depths per workgroup: 32 (N = 128), 16 (256), 8 (512)
+// Shape of the transform at N columns.
 template <int NN>
-__host__ __device__ constexpr int ft_depths() { return NN == 128 ? 32 : (NN == 256 ? 16 : 8); }
+struct FtShape {
+  static_assert(NN % 32 == 0 && NN >= 32 && NN <= 512, "lateral sizes 32 .. 512 in steps of 32");
+  static constexpr int R = NN > 256 ? 2 : 1;                       // parities of q transformed apart
+  static constexpr int K = NN / 16 / R;                            // stage-3 points
+  static constexpr int DG = K <= 2 ? 8 : (K <= 4 ? 4 : (K <= 8 ? 2 : 1));   // depths per lane group
+  static constexpr int CW = 16 / DG;                               // stage-1 columns (lanes) per depth
+};
+// depths per workgroup: 16 DG, 8 where a wave holds both parities
+template <int NN>
+__host__ __device__ constexpr int ft_depths() { return 16 * FtShape<NN>::DG / FtShape<NN>::R; }
+inline int ft_depths_of(int n) { return n > 256 ? 8 : (n > 128 ? 16 : (n > 64 ? 32 : (n > 32 ? 64 : 128))); }
 
-// LDS: staged bins [2][ff_stage_rows], stage twiddles [16 x1][16 j], (N = 512) combination
+// LDS: staged bins [2][ff_stage_rows], stage twiddles [16 x1][16 j], (N > 256) combination
 // twiddles [2 e][16 x2][16 j], transpose blocks [4 waves][4 groups][kFtTr].
 template <int NN>
-__host__ __device__ constexpr int ft_twiddles() { return NN == 512 ? 768 : 256; }
+__host__ __device__ constexpr int ft_twiddles() { return NN > 256 ? 768 : 256; }
 template <int NSUB, int NN = 256>
 inline size_t k3fft_lds() {
   return (size_t)(2 * ff_stage_rows<NSUB, NN / 16>() + ft_twiddles<NN>() + kFtWaves * 4 * kFtTr) * sizeof(float2);
 }
 
-// The 16-byte pieces of a bin's staged inputs, 256 per pass (one per thread): one pass at
-// N = 128 and 256 (N = 128 with three sub-apertures fills it exactly), two parts of two
-// passes at N = 512.  Separate members (not an array) so that they stay in registers.
+// The 16-byte pieces of a bin's staged inputs, 256 per pass (one per thread): one pass up to
+// N = 128 (which three sub-apertures fill exactly), two up to 256, two parts of two passes
+// beyond.  Separate members (not an array) so that they stay in registers.
 template <int NSUB, int NN>
 struct FtPiece {
   typedef FfRows<NSUB, NN / 16> P;
-  static constexpr int R = NN == 512 ? 2 : 1;
+  static constexpr int R = FtShape<NN>::R;
   uint4 v0, v1, v2, v3;
   int d0, d1, d2, d3;
   __device__ FtPiece(int tid) {
@@ -73,7 +93,7 @@ struct FtPiece {
     d2 = R > 1 ? P::where(tid + 512) : -1;
     d3 = R > 1 ? P::where(tid + 768) : -1;
   }
-  // pieces 0, 1 (part 0) and, at N = 512, pieces 2, 3 (part 1): the kernel moves the two
+  // pieces 0, 1 (part 0) and, beyond N = 256, pieces 2, 3 (part 1): the kernel moves the two
   // parts at different points of a bin so that only two are in registers at a time
   __device__ __forceinline__ void load(const K3Args& a, int f, int b, int tid, int part) {
     if (part == 0) {
@@ -207,45 +227,88 @@ __device__ __forceinline__ void idft8(float2 (&v)[16], int o) {
   }
 }
 
+// The K-point transforms of stage 3, depth D's at p[D CW ..].
+template <int K, int O>
+__device__ __forceinline__ void idft_at(float2 (&p)[16]) {
+  if constexpr (K == 16) idft16(p);
+  else if constexpr (K == 8) idft8(p, O);
+  else dft_small<1, K, O>(p);
+}
+template <int NN, int... D>
+__device__ __forceinline__ void stage3(float2 (&p)[16], std::integer_sequence<int, D...>) {
+  (idft_at<FtShape<NN>::K, D * FtShape<NN>::CW>(p), ...);
+}
+
+// kz(q) = kz(N - q), so the propagator of a column's m = 9 .. 15 is that of another column's 15 - m at the same
+// depth.  N <= 256 (q = K m + q2): N - q = K (15 - m) + (K - q2), column K - q2 of the same CW lanes; column 0 pairs
+// with itself as H[16 - m] (the caller's case).  N > 256 (q = 2 K m + 2 j + e): columns K - j in the even-q rows,
+// K - 1 - j in the odd-q rows.  This returns the partner column's value: a DPP rotation of the row of 16 lanes by n
+// (lane i takes lane i - n) and a mirror of the row (15 - i) or of its halves (7 - i), so lane i receives lane
+// 15 - n - i or 7 - n - i; rows 0, 2 (even q) and 1, 3 (odd q) rotate apart through the row mask.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+template <int NN>
+__device__ __forceinline__ float partner_column(float v) {
+  typedef FtShape<NN> F;
+  constexpr int K = F::K;
+  if constexpr (F::R == 2) {
+    constexpr int even = (15 - K) & 15, odd = (16 - K) & 15;
+    const int x = __builtin_bit_cast(int, v);
+    int t = x;
+    if constexpr (even > 0) t = __builtin_amdgcn_update_dpp(t, x, 0x120 + even, 0x5, 0xF, false);
+    if constexpr (odd > 0) t = __builtin_amdgcn_update_dpp(t, x, 0x120 + odd, 0xA, 0xF, false);
+    return dpp_mov<0x140>(__builtin_bit_cast(float, t));
+  } else if constexpr (F::CW == 16) {
+    return dpp_mov<0x140>(dpp_mov<0x120 + ((15 - K) & 15)>(v));
+  } else if constexpr (F::CW == 8) {
+    return dpp_mov<0x141>(dpp_mov<0x120 + ((7 - K) & 15)>(v));
+  } else if constexpr (F::CW == 4) {
+    return dpp_mov<0x6C>(v);                     // quad permutation [0, 3, 2, 1]
+  } else {
+    return v;                                    // K = 2: column 1 pairs with itself
+  }
+}
+
 template <int NSUB, bool COH = false, int NN = 256>
 __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
   static_assert(!COH || (NSUB == 1 && NN == 256), "pair cross-spectra come with the full-aperture sums at N = 256");
-  static_assert(NN == 128 || NN == 256 || NN == 512, "N = 128, 256 or 512");
   constexpr int NP = AccCount<NSUB>::pairs;
   constexpr int N = NN;
-  constexpr int R = NN == 512 ? 2 : 1;
-  constexpr bool HALF = NN == 128;
+  constexpr int R = FtShape<NN>::R, K = FtShape<NN>::K, DG = FtShape<NN>::DG, CW = FtShape<NN>::CW;
+  constexpr int PX = DG * K;                                       // pixels per lane
   constexpr int ROWS = NN / 16;
   extern __shared__ float2 lds_ft[];
   float2* stage = lds_ft;                                          // [2][ff_stage_rows]
   float2* twl = lds_ft + 2 * ff_stage_rows<NSUB, ROWS>();          // [16 x1][16 j] (+ [2 e][16 x2][16 j])
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int g = lane >> 4, j = lane & 15;
-  const int e = R == 2 ? (g & 1) : 0;                              // parity of q (N = 512)
+  const int e = R == 2 ? (g & 1) : 0;                              // parity of q (N > 256)
   float2* tr = twl + ft_twiddles<NN>() + (w * 4 + g) * kFtTr;     // this group's transpose block
-  // staged row of this lane's stage-1 inputs
-  const int srow = HALF ? (j & 7) : (R == 1 ? j : 2 * j + e);
+  // stage-1 column of this lane (idle lanes repeat the last one) and its staged row
+  const int col = K == CW ? j % CW : min(j % CW, K - 1);
+  const int srow = R == 1 ? col : 2 * col + e;
   K3Args a = a0;
   const WgFF wg(a, wg_group(a, grp));
   const int f = wg.f;
   // first depth of the lane's pixels, and the depth of its stage-1 column
-  const int depth = HALF ? wg.dt * ft_depths<NN>() + 8 * w + 2 * g
-                         : (R == 1 ? wg.dt * ft_depths<NN>() + 4 * w + g : wg.dt * ft_depths<NN>() + 2 * w + (g >> 1));
-  const int depth1 = HALF ? depth + (j >> 3) : depth;
+  const int depth = wg.dt * ft_depths<NN>() + (R == 1 ? (4 * w + g) * DG : 2 * w + (g >> 1));
+  const int depth1 = depth + j / CW;
   const double z = depth1 < a.n_z ? a.z[depth1] : 0.0;
 
-  // stage-1 -> stage-3 twiddles e^{2 pi i q2 x1 / 256} and (N = 512) the combination twiddles
-  // e^{2 pi i (j + 16 x2 + 256 e) / 512}, the e = 1 half the negated e = 0 half (FP32 tables built in FP64)
+  // stage-1 -> stage-3 twiddles e^{2 pi i q2 x1 / 16 K} and (N > 256) the combination twiddles
+  // e^{2 pi i (j + 16 x2 + e N/2) / N}, the e = 1 half the negated e = 0 half (FP32 tables built in FP64)
   for (int k = tid; k < ft_twiddles<NN>(); k += 256) {
     const float2 t = k < 256 ? a.ff_tw_vec[k] : a.ff_tw2_vec[(k - 256) & 255];
     twl[k] = k < 512 ? t : make_float2(-t.x, -t.y);
   }
 
-  float accS[NSUB][16];
-  float accC[NP > 0 ? NP : 1][16];
-  float accG[COH ? 4 : 1][16];
+  float accS[NSUB][PX];
+  float accC[NP > 0 ? NP : 1][PX];
+  float accG[COH ? 4 : 1][PX];
 #pragma unroll
-  for (int x2 = 0; x2 < 16; ++x2) {
+  for (int x2 = 0; x2 < PX; ++x2) {
 #pragma unroll
     for (int i = 0; i < NSUB; ++i) accS[i][x2] = 0.f;
 #pragma unroll
@@ -269,14 +332,9 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
     if (more) pc.load(a, f, b + 1, tid, 0);
     const float2* st = stage + ((b - wg.b_begin) & 1) * ff_stage_rows<NSUB, ROWS>();
     const double* kzr = reinterpret_cast<const double*>(st + NSUB * ROWS * kFfRow) + srow * kFfRow;
-    // propagator at q = 16 m + j (N = 256) or 32 m + 2 j + e (N = 512) (Eq. 2): phase in FP64 reduced to [-1/2, 1/2] cycle,
-    // hardware sin/cos; evanescent values replaced in a branch only lanes holding any take.
-    // kz(q) = kz(N - q).  At N = 256, N - (16 m + j) = 16 (15 - m) + (16 - j): lane j's H[m] for m > 8 is lane
-    // (16 - j)'s H[15 - m] (same depth), and lane 0's is its own H[16 - m].  At N = 512 the even-q rows (e = 0)
-    // pair the same way, N - (32 m + 2 j) = 32 (15 - m) + 2 (16 - j), and in the odd-q rows
-    // N - (32 m + 2 j + 1) = 32 (15 - m) + 2 (15 - j) + 1 pairs lane j with lane 15 - j, none with itself.  At
-    // N = 128 (q = 8 m + q2, q2 = j % 8, one depth per 8 lanes) the partner of q2 is 8 - q2 in the same 8 lanes,
-    // and q2 = 0 pairs with itself.  So a lane computes H[0..8] and takes the other seven from its partner lane.
+    // propagator at q = K m + col or 2 K m + 2 col + e (Eq. 2): phase in FP64 reduced to [-1/2, 1/2] cycle, hardware
+    // sin/cos; evanescent values replaced in a branch only lanes holding any take.  A lane computes H[0..8] and takes
+    // the other seven from its partner column (partner_column above).
     constexpr int MD = 9;   // values computed directly
     float2 H[16];
 #pragma unroll
@@ -291,13 +349,10 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
         if (kzr[m] < 0.0) H[m] = propagator(z, kzr[m], a.zero_evanescent);
     }
     {
-      const bool self = (HALF ? (j & 7) : j) == 0 && e == 0;
+      const bool self = col == 0 && e == 0;
 #pragma unroll
       for (int m = MD; m < 16; ++m) {
-        const float2 o =
-            HALF     ? make_float2(lane_mirror8(H[15 - m].x), lane_mirror8(H[15 - m].y))
-            : R == 2 ? make_float2(lane_mirror16_odd_rows15(H[15 - m].x), lane_mirror16_odd_rows15(H[15 - m].y))
-                     : make_float2(lane_mirror16(H[15 - m].x), lane_mirror16(H[15 - m].y));
+        const float2 o = make_float2(partner_column<NN>(H[15 - m].x), partner_column<NN>(H[15 - m].y));
         H[m] = self ? H[16 - m] : o;
       }
     }
@@ -316,9 +371,9 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
     for (int i = 0; i < NSUB; ++i) {
       idft16(p[i]);                                                // Y(x1, q2 = j), x1 = 0..15
 #pragma unroll
-      for (int x1 = 0; x1 < 16; ++x1)   // (the twiddle of x1 = 0 is exactly 1; skipped at N = 512 only,
-                                        // where it shortens the spill, 76 -> 20 bytes a lane; at N = 128
-                                        // and 256 the compiler's allocation then spills)
+      for (int x1 = 0; x1 < 16; ++x1)   // (the twiddle of x1 = 0 is exactly 1; skipped beyond N = 256 only,
+                                        // where it shortens the spill, at N = 512 76 -> 20 bytes a lane; at
+                                        // N = 128 and 256 the compiler's allocation then spills)
         tr[x1 * kFfRow + j] = (R == 2 && x1 == 0) ? p[i][0] : cmul(p[i][x1], twl[x1 * 16 + j]);
       __builtin_amdgcn_wave_barrier();
       const float4* yr = reinterpret_cast<const float4*>(tr + j * kFfRow);   // row x1 = j
@@ -329,17 +384,12 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
         p[i][2 * k + 1] = make_float2(yy.z, yy.w);
       }
       __builtin_amdgcn_wave_barrier();
-      if constexpr (HALF) {
-        idft8(p[i], 0);                                            // depth + 0: p(j + 16 x2), x2 = 0..7
-        idft8(p[i], 8);                                            // depth + 1
-      } else {
-        idft16(p[i]);                                              // p(j + 16 x2), x2 = 0..15
-      }
+      stage3<NN>(p[i], std::make_integer_sequence<int, DG>());     // depth d: p(j + 16 x2) in p[i][d CW + x2]
       if constexpr (R == 2) {
-        // p(x' + 256 e) = P_0(x') + w P_1(x'), x' = j + 16 x2, w = e^{2 pi i (x' + 256 e) / 512}: the even row of
+        // p(x' + e N/2) = P_0(x') + w P_1(x'), x' = j + 16 x2, w = e^{2 pi i (x' + e N/2) / N}: the even row of
         // each row pair (e = 0) holds P_0(x'), the odd row P_1(x'), and one row swap hands both to both rows
 #pragma unroll
-        for (int x2 = 0; x2 < 16; ++x2) {
+        for (int x2 = 0; x2 < K; ++x2) {
           const float2 re = rows_even_odd(p[i][x2].x), im = rows_even_odd(p[i][x2].y);   // (P_0, P_1) parts
           const float2 w2 = twl[256 + 256 * e + x2 * 16 + j];
           p[i][x2] = make_float2(fmaf(w2.x, re.y, fmaf(-w2.y, im.y, re.x)), fmaf(w2.x, im.y, fmaf(w2.y, re.y, im.x)));
@@ -355,24 +405,25 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
     }
     // fold: S_i = sum |p_i|^2, C_ij = sum Re(p_i conj p_j) (Eq. 4) over the bins
 #pragma unroll
-    for (int x2 = 0; x2 < 16; ++x2) {
+    for (int px = 0; px < PX; ++px) {
+      const int x2 = px / K * CW + px % K;                         // of depth px / K
 #pragma unroll
-      for (int i = 0; i < NSUB; ++i) accS[i][x2] = fmaf(p[i][x2].x, p[i][x2].x, fmaf(p[i][x2].y, p[i][x2].y, accS[i][x2]));
+      for (int i = 0; i < NSUB; ++i) accS[i][px] = fmaf(p[i][x2].x, p[i][x2].x, fmaf(p[i][x2].y, p[i][x2].y, accS[i][px]));
       if constexpr (NSUB == 3) {
-        accC[0][x2] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][x2]));
-        accC[1][x2] = fmaf(p[1][x2].x, p[2][x2].x, fmaf(p[1][x2].y, p[2][x2].y, accC[1][x2]));
-        accC[2][x2] = fmaf(p[2][x2].x, p[0][x2].x, fmaf(p[2][x2].y, p[0][x2].y, accC[2][x2]));
+        accC[0][px] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][px]));
+        accC[1][px] = fmaf(p[1][x2].x, p[2][x2].x, fmaf(p[1][x2].y, p[2][x2].y, accC[1][px]));
+        accC[2][px] = fmaf(p[2][x2].x, p[0][x2].x, fmaf(p[2][x2].y, p[0][x2].y, accC[2][px]));
       } else if constexpr (NSUB == 2) {
-        accC[0][x2] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][x2]));
+        accC[0][px] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][px]));
       }
       if constexpr (COH) {
         const float pr = p[0][x2].x, pi = p[0][x2].y;
         const float lr = lane_xor1(pr), li = lane_xor1(pi);
         const float zr = lane_xor16(pr), zi = lane_xor16(pi);
-        accG[0][x2] = fmaf(pr, lr, fmaf(pi, li, accG[0][x2]));
-        accG[1][x2] = fmaf(pi, lr, fmaf(-pr, li, accG[1][x2]));
-        accG[2][x2] = fmaf(pr, zr, fmaf(pi, zi, accG[2][x2]));
-        accG[3][x2] = fmaf(pi, zr, fmaf(-pr, zi, accG[3][x2]));
+        accG[0][px] = fmaf(pr, lr, fmaf(pi, li, accG[0][px]));
+        accG[1][px] = fmaf(pi, lr, fmaf(-pr, li, accG[1][px]));
+        accG[2][px] = fmaf(pr, zr, fmaf(pi, zi, accG[2][px]));
+        accG[3][px] = fmaf(pi, zr, fmaf(-pr, zi, accG[3][px]));
       }
     }
     if (more) pc.store(nxt, R - 1);
@@ -382,11 +433,11 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
   const size_t plane = (size_t)a.n_z * N;
   float* base = a.accum + ((size_t)wg.sp * a.F + f) * NA * plane;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    // pixel of register k: (depth + k / 8, j + 16 (k % 8)) at N = 128, (depth, j + 16 k + 256 e) otherwise
-    const int d = HALF ? depth + (k >> 3) : depth;
+  for (int k = 0; k < PX; ++k) {
+    // pixel of register k: (depth + k / K, j + 16 (k % K) + e N/2)
+    const int d = depth + k / K;
     if (d >= a.n_z) continue;
-    float* dst = base + (size_t)d * N + j + (HALF ? 16 * (k & 7) : 16 * k + 256 * e);
+    float* dst = base + (size_t)d * N + j + 16 * (k % K) + (N / 2) * e;
 #pragma unroll
     for (int i = 0; i < NSUB; ++i) dst[i * plane] = accS[i][k];
 #pragma unroll

@@ -1,4 +1,5 @@
-// K3: fused propagate + inverse lateral transform (DFT-GEMM on the matrix cores)
+// K3 for the 16-bit operand forms (sizes without a factored kernel): fused propagate +
+// inverse lateral transform (DFT-GEMM on the matrix cores)
 // + sums over frequency of the sub-aperture cross-spectra.
 //
 // GEMM view for one (frame, bin): rows = depths, K = N slots, columns = x.
@@ -23,76 +24,12 @@
 
 namespace pam {
 
-// Stage geometry shared by the FP32 and 16-bit kernels.
+// Stage geometry.
 struct StageMap {
   int b_begin, nch;
   __device__ __forceinline__ int bin(int s) const { return b_begin + s / nch; }
   __device__ __forceinline__ int chunk(int s) const { return s - (s / nch) * nch; }
 };
-
-// Generation items.  Producer thread ptid owns items e = ptid + k * npt of every
-// stage: row r = e & 31 of the depth tile and slot pair ql = e >> 5 (slots 2ql and
-// 2ql + 1 of the stage's chunk).  The row, hence the depth, is fixed across stages;
-// a negative depth marks a row beyond the grid (zero propagator).
-template <int GEN>
-struct GenRows {
-  double z[GEN];
-  __device__ GenRows(const K3Args& a, int ptid, int npt, int d0) {
-#pragma unroll
-    for (int k = 0; k < GEN; ++k) {
-      const int d = d0 + ((ptid + k * npt) & 31);
-      z[k] = d < a.n_z ? a.z[d] : -1.0;
-    }
-  }
-};
-
-// Global inputs of one stage for one producer thread: kz / (2 pi) at each item's q,
-// at q = N/2 (slot 1 holds cos(pi x)), the coefficients of slots 2q, 2q+1 of every
-// sub-aperture, and the thread's share of the stage's basis tile.
-template <int NSUB, int GEN, typename BT, int CPY>
-struct StageIn {
-  double kz[GEN];
-  double kz_half;
-  float4 g[GEN][NSUB];
-  BT bc[CPY];
-};
-
-template <int NSUB, int GEN, typename BT, int CPY>
-__device__ __forceinline__ void load_gen_inputs(const K3Args& a, int f, int b, int q0, int ptid, int npt,
-                                                StageIn<NSUB, GEN, BT, CPY>& in) {
-  const int N = a.N;
-  const double* kzb = a.kz + (size_t)b * kz_row(N);
-  in.kz_half = kzb[N / 2];
-  const float2* g = a.coeffs + ((size_t)f * a.n_sel + b) * NSUB * N;
-#pragma unroll
-  for (int k = 0; k < GEN; ++k) {
-    const int q = q0 + ((ptid + k * npt) >> 5);
-    in.kz[k] = kzb[q];
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i) in.g[k][i] = *reinterpret_cast<const float4*>(g + (size_t)i * N + 2 * q);
-  }
-}
-
-// A values of item k: vals[t][0..1] = A_t[r, 2ql], A_t[r, 2ql + 1] for every tile t.
-template <int NSUB, int GEN, typename BT, int CPY>
-__device__ __forceinline__ void gen_values(const K3Args& a, double z, const StageIn<NSUB, GEN, BT, CPY>& in, int k,
-                                           bool q_is_zero, float vals[2 * NSUB][2]) {
-  float2 h0 = make_float2(0.f, 0.f), h1 = h0;
-  if (z >= 0.0) {
-    h0 = propagator(z, in.kz[k], a.zero_evanescent);
-    h1 = q_is_zero ? propagator(z, in.kz_half, a.zero_evanescent) : h0;
-  }
-#pragma unroll
-  for (int i = 0; i < NSUB; ++i) {
-    const float4 gg = in.g[k][i];
-    const float2 a0 = cmul(h0, make_float2(gg.x, gg.y));
-    const float2 a1 = cmul(h1, make_float2(gg.z, gg.w));
-    vals[2 * i][0] = a0.x;
-    vals[2 * i][1] = a1.x;
-    vals[2 * i + 1][0] = a0.y;
-    vals[2 * i + 1][1] = a1.y;
-  }
-}
 
 template <int NSUB, int XT>
 __device__ __forceinline__ void fold_bin(const v16f (&C)[XT][2 * NSUB], float inv,
@@ -156,142 +93,6 @@ __device__ __forceinline__ void store_acc(const K3Args& a, int sp, int f, int d0
 // their loops are separate so the consumers' 192 accumulator registers are not
 // live in the producer code.
 // ---------------------------------------------------------------------------
-
-// FP32 operands on v_mfma_f32_32x32x2_f32 (K = 2 slots per instruction).
-// LDS: A [2][2 NSUB][KC][32] and B [2][KC][WC] floats.
-template <int NSUB, int NC>
-__global__ __launch_bounds__(NC * 128, 1) void k3_fields_fp32(K3Args a) {
-  constexpr int NT = 2 * NSUB;
-  constexpr int NP = AccCount<NSUB>::pairs;
-  constexpr int KC = 32;
-  constexpr int WC = NC * 32;
-  constexpr int NPT = NC * 64;                 // producer threads
-  constexpr int A_SZ = NT * KC * 32;
-  constexpr int B_SZ = KC * WC;
-  constexpr int GEN = 32 * (KC / 2) / NPT;     // generation items per producer thread per stage
-  constexpr int CPY = (KC * WC / 4) / NPT;     // float4 basis copies per producer thread per stage
-  static_assert(GEN >= 1 && (32 * (KC / 2)) % NPT == 0, "generation split");
-  static_assert(CPY >= 1 && (KC * WC / 4) % NPT == 0, "basis copy split");
-  extern __shared__ float smem[];
-  float* Abuf = smem;                 // [2][A_SZ]
-  float* Bbuf = smem + 2 * A_SZ;      // [2][B_SZ]
-
-  const int N = a.N;
-  int bid = blockIdx.x;
-  const int sp = bid % a.n_split; bid /= a.n_split;
-  const int xg = bid % a.n_xg;    bid /= a.n_xg;
-  const int dt = bid % a.n_dt;    bid /= a.n_dt;
-  const int f = bid;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int xwg = xg * WC;
-  const int d0 = dt * 32;
-  const int b_begin = sp * a.bins_per_split;
-  const int b_end = min(a.n_sel, b_begin + a.bins_per_split);
-  const StageMap sm{b_begin, N / KC};
-  const int S = (b_end - b_begin) * sm.nch;
-
-  if (w >= NC) {
-    // ---------------- producer ----------------
-    const int ptid = tid - NC * 64;
-    const GenRows<GEN> rows(a, ptid, NPT, d0);
-    StageIn<NSUB, GEN, float4, CPY> cur, nxt;
-    auto load = [&](int s, StageIn<NSUB, GEN, float4, CPY>& in) {
-      const int c = sm.chunk(s);
-      load_gen_inputs<NSUB, GEN>(a, f, sm.bin(s), c * (KC / 2), ptid, NPT, in);
-#pragma unroll
-      for (int k = 0; k < CPY; ++k) {
-        const int e = ptid + k * NPT;
-        const int row = e / (WC / 4), c4 = e - row * (WC / 4);
-        in.bc[k] = reinterpret_cast<const float4*>(a.basis + (size_t)(c * KC + row) * N + xwg)[c4];
-      }
-    };
-    auto store = [&](int s, const StageIn<NSUB, GEN, float4, CPY>& in, float* Ab, float4* Bb) {
-      const int c0q = sm.chunk(s) * (KC / 2);
-#pragma unroll
-      for (int k = 0; k < GEN; ++k) {
-        const int e = ptid + k * NPT;
-        const int r = e & 31, ql = e >> 5;
-        float vals[NT][2];
-        gen_values<NSUB>(a, rows.z[k], in, k, c0q + ql == 0, vals);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          Ab[(t * KC + 2 * ql) * 32 + r] = vals[t][0];
-          Ab[(t * KC + 2 * ql + 1) * 32 + r] = vals[t][1];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < CPY; ++k) Bb[ptid + k * NPT] = in.bc[k];
-    };
-    // inputs of stage s+2 are in flight while stage s+1 is generated; the two
-    // input sets swap roles every stage (no register copies, so no wait on loads
-    // still in flight)
-    if (S > 0) {
-      load(0, cur);
-      store(0, cur, Abuf, reinterpret_cast<float4*>(Bbuf));
-    }
-    if (S > 1) load(1, cur);
-    __syncthreads();
-    // Loads are unconditional (the last stage's inputs are re-read past the end) so
-    // the in-flight registers never merge with older values at a branch.
-    auto step = [&](int s, StageIn<NSUB, GEN, float4, CPY>& gen, StageIn<NSUB, GEN, float4, CPY>& fill) {
-      load(min(s + 2, S - 1), fill);
-      store(s + 1, gen, Abuf + ((s + 1) & 1) * A_SZ, reinterpret_cast<float4*>(Bbuf + ((s + 1) & 1) * B_SZ));
-      __syncthreads();
-    };
-    int s = 0;
-    for (; s + 2 < S; s += 2) {
-      step(s, cur, nxt);
-      step(s + 1, nxt, cur);
-    }
-    if (s + 1 < S) {
-      step(s, cur, nxt);
-      ++s;
-    }
-    if (S > 0) __syncthreads();   // stage S-1: nothing left to generate
-    return;
-  }
-
-  // ---------------- consumer ----------------
-  const int half = lane >> 5, col = lane & 31;
-  float accS[1][NSUB][16];
-  float accC[1][NP > 0 ? NP : 1][16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i) accS[0][i][v] = 0.f;
-#pragma unroll
-    for (int p = 0; p < (NP > 0 ? NP : 1); ++p) accC[0][p][v] = 0.f;
-  }
-  v16f C[1][NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) C[0][t][v] = 0.f;
-
-  __syncthreads();
-  for (int s = 0; s < S; ++s) {
-    const float* Ac = Abuf + (s & 1) * A_SZ;
-    const float* Bc = Bbuf + (s & 1) * B_SZ;
-#pragma unroll
-    for (int j = 0; j < KC / 2; ++j) {
-      const float bv = Bc[(2 * j + half) * WC + w * 32 + col];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const float av = Ac[(t * KC + 2 * j + half) * 32 + col];
-        C[0][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, C[0][t], 0, 0, 0);
-      }
-    }
-    if (sm.chunk(s) == sm.nch - 1) {
-      fold_bin<NSUB, 1>(C, a.inv_scale[(size_t)f * a.n_sel + sm.bin(s)], accS, accC);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) C[0][t][v] = 0.f;
-    }
-    __syncthreads();
-  }
-  store_acc<NSUB, 1>(a, sp, f, d0, xwg + w * 32, lane, accS, accC);
-}
 
 // Generation items of the 16-bit kernels: four consecutive slots (two slot
 // pairs) of one row, so each A plane is written with one 8-byte LDS store per
@@ -543,10 +344,6 @@ __global__ __launch_bounds__(NC * 128, 1) void k3_fields_split(K3Args a) {
 }
 
 // LDS bytes of the kernels above (double-buffered A and basis tiles)
-template <int NSUB, int NC>
-constexpr size_t k3_fp32_lds() {
-  return (size_t)2 * (2 * NSUB * 32 * 32 + 32 * NC * 32) * sizeof(float);
-}
 template <int PASSES, int NSUB, int NC>
 constexpr size_t k3_split_lds() {
   return (size_t)2 * ((2 * NSUB) * (PASSES == 3 ? 2 : 1) * 32 * 40 + (PASSES == 3 ? 2 : 1) * NC * 32 * 40) * 2;

@@ -11,7 +11,6 @@
 // rows-of-16 and CT B tiles per step instead of 6 A rows-of-32 and one B tile.
 //
 // Matrix-core layouts (16 x 16 output, lane l):
-//   v_mfma_f32_16x16x4_f32:   A[l%16][l/16],        B[l/16][l%16]
 //   v_mfma_f32_16x16x32_{bf16,f16}: A[l%16][8(l/16)+j], B[8(l/16)+j][l%16], j = 0..7
 //   result v = 0..3:          C[4(l/16) + v][l%16]
 #pragma once
@@ -144,7 +143,7 @@ struct Wg16 {
   }
 };
 
-// Producer pipeline shared by both kernels: inputs of stage s+2 are loaded while
+// Producer pipeline: inputs of stage s+2 are loaded while
 // stage s+1 is generated, the two input sets alternate (no register copies), and
 // loads are unconditional (the last stage's inputs are re-read past the end).
 // One barrier per stage, matching the consumer loop: 1 + S barriers in total.
@@ -168,119 +167,6 @@ __device__ __forceinline__ void produce(int S, In& cur, In& nxt, Load&& load, St
   }
   if (s + 1 < S) step(s, cur, nxt);
   if (S > 0) __syncthreads();   // stage S-1: nothing left to generate
-}
-
-// ---------------------------------------------------------------------------
-// FP32 operands on v_mfma_f32_16x16x4_f32.
-// LDS: A [2][2 NSUB][16 rows][34] floats (slot pairs adjacent; the 34-float row
-// pitch keeps the producers' 8-byte stores and the consumers' 4-byte reads free
-// of bank conflicts) and B [2][32 slots][64 CT + 16] floats.
-// Producer thread p owns row p & 15 and slot pair p >> 4 of every stage.
-// ---------------------------------------------------------------------------
-template <int NSUB, int CT>
-__global__ __launch_bounds__(512, 1) void k3f16_fp32(K3Args a) {
-  constexpr int NT = 2 * NSUB;
-  constexpr int NP = AccCount<NSUB>::pairs;
-  constexpr int KC = 32, DR = 16, NC = 4, NPT = 256;
-  constexpr int WCOLS = NC * CT * 16;
-  constexpr int SP = KC + 2;
-  constexpr int WCP = WCOLS + 16;
-  constexpr int A_SZ = NT * DR * SP;
-  constexpr int B_SZ = KC * WCP;
-  constexpr int CPY = KC * WCOLS / 4 / NPT;
-  static_assert(CPY >= 1 && (KC * WCOLS / 4) % NPT == 0, "basis copy split");
-  extern __shared__ float smem[];
-  float* Abuf = smem;
-  float* Bbuf = smem + 2 * A_SZ;
-
-  const Wg16 wg(a, KC);
-  const int N = a.N, S = wg.S, f = wg.f;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int d0 = wg.dt * DR, xwg = wg.xg * WCOLS;
-
-  if (w >= NC) {
-    const int ptid = tid - NC * 64;
-    const int r = ptid & 15, ql = ptid >> 4;
-    const double z = d0 + r < a.n_z ? a.z[d0 + r] : -1.0;
-    typedef PairIn<NSUB, float4, CPY> In;
-    In cur, nxt;
-    auto load = [&](int s, In& in) {
-      const int c = wg.sm.chunk(s);
-      load_pair_inputs<NSUB>(a, f, wg.sm.bin(s), c * (KC / 2) + ql, in);
-#pragma unroll
-      for (int k = 0; k < CPY; ++k) {
-        const int e = ptid + k * NPT;
-        const int srow = e / (WCOLS / 4), c4 = e - srow * (WCOLS / 4);
-        in.bc[k] = reinterpret_cast<const float4*>(a.basis + (size_t)(c * KC + srow) * N + xwg)[c4];
-      }
-    };
-    auto store = [&](int s, const In& in) {
-      float* Ab = Abuf + (s & 1) * A_SZ;
-      float* Bb = Bbuf + (s & 1) * B_SZ;
-      float vals[NT][2];
-      gen_pair<NSUB>(a, z, in, wg.sm.chunk(s) == 0 && ql == 0, vals);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        *reinterpret_cast<float2*>(Ab + (t * DR + r) * SP + 2 * ql) = make_float2(vals[t][0], vals[t][1]);
-#pragma unroll
-      for (int k = 0; k < CPY; ++k) {
-        const int e = ptid + k * NPT;
-        const int srow = e / (WCOLS / 4), c4 = e - srow * (WCOLS / 4);
-        *reinterpret_cast<float4*>(Bb + srow * WCP + 4 * c4) = in.bc[k];
-      }
-    };
-    produce(S, cur, nxt, load, store);
-    return;
-  }
-
-  // ---------------- consumer ----------------
-  const int lr = lane & 15, lk = lane >> 4;
-  const int xw = w * CT * 16;
-  float accS[CT][NSUB][4];
-  float accC[CT][NP > 0 ? NP : 1][4];
-  v4f C[NT][CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-#pragma unroll
-      for (int i = 0; i < NSUB; ++i) accS[ct][i][v] = 0.f;
-#pragma unroll
-      for (int p = 0; p < (NP > 0 ? NP : 1); ++p) accC[ct][p][v] = 0.f;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) C[t][ct][v] = 0.f;
-    }
-
-  __syncthreads();
-  for (int s = 0; s < S; ++s) {
-    const float* Ac = Abuf + (s & 1) * A_SZ;
-    const float* Bc = Bbuf + (s & 1) * B_SZ;
-    const bool last = wg.sm.chunk(s) == wg.sm.nch - 1;
-    const float inv = last ? a.inv_scale[(size_t)f * a.n_sel + wg.sm.bin(s)] : 0.f;
-#pragma unroll
-    for (int j = 0; j < KC / 4; ++j) {
-      float bv[CT];
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) bv[ct] = Bc[(4 * j + lk) * WCP + xw + 16 * ct + lr];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const float av = Ac[(t * DR + lr) * SP + 4 * j + lk];
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) C[t][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[ct], C[t][ct], 0, 0, 0);
-      }
-    }
-    if (last) {
-      fold_bin16<NSUB, CT>(C, inv, accS, accC);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) C[t][ct][v] = 0.f;
-    }
-    __syncthreads();
-  }
-  store_acc16<NSUB, CT>(a, wg.sp, f, d0, xwg + xw, lane, accS, accC);
 }
 
 // ---------------------------------------------------------------------------
@@ -424,11 +310,7 @@ __global__ __launch_bounds__(512, 1) void k3f16_split(K3Args a) {
   store_acc16<NSUB, CT>(a, wg.sp, f, d0, xwg + xw, lane, accS, accC);
 }
 
-// LDS bytes of the kernels above
-template <int NSUB, int CT>
-constexpr size_t k3f16_fp32_lds() {
-  return (size_t)2 * ((2 * NSUB) * 16 * 34 + 32 * (64 * CT + 16)) * sizeof(float);
-}
+// LDS bytes of the kernel above
 template <int PASSES, int NSUB, int CT>
 constexpr size_t k3f16_split_lds() {
   return (size_t)2 * ((2 * NSUB) * (PASSES == 3 ? 2 : 1) * 16 * 40 + (PASSES == 3 ? 2 : 1) * 64 * CT * 40) * 2;

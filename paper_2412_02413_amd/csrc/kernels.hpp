@@ -92,22 +92,6 @@ __device__ __forceinline__ float lane_xor16(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
 }
 
-// The value lane (16 - i) mod 16 of the lane's row of 16 holds (i = lane index in the row): a DPP row
-// rotation by 15 (lane i takes lane i + 1 mod 16) followed by a DPP row mirror (lane i takes lane 15 - i).
-__device__ __forceinline__ float lane_mirror16(float v) {
-  const int t = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x12F, 0xF, 0xF, false);
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(t, 0x140, 0xF, 0xF, false));
-}
-
-// Rows 0 and 2 of the wave: the value lane (16 - i) mod 16 of the row holds, as lane_mirror16; rows 1 and 3: the
-// value lane 15 - i holds.  The rotation is written to rows 0 and 2 only (DPP row mask 0b0101; the other rows keep
-// their own values), then every row is mirrored.
-__device__ __forceinline__ float lane_mirror16_odd_rows15(float v) {
-  const int x = __builtin_bit_cast(int, v);
-  const int t = __builtin_amdgcn_update_dpp(x, x, 0x12F, 0x5, 0xF, false);
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(t, 0x140, 0xF, 0xF, false));
-}
-
 // Rows 2r and 2r + 1 of the wave as a pair: every lane i of both rows receives lane i of the even row in .x and
 // lane i of the odd row in .y (v_permlane16_swap of a register with itself swaps the odd row of the first
 // operand with the even row of the second).
@@ -115,14 +99,6 @@ __device__ __forceinline__ float2 rows_even_odd(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return make_float2(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
-}
-
-// The value lane (8 - i) mod 8 of the lane's group of 8 holds (i = lane index in the group), for i = 1..7: the
-// row rotation by 15 (lane i takes lane i + 1 mod 16) followed by a DPP half-row mirror (lane i takes lane 7 - i
-// of its 8).  Lane 0 of each group receives a value from outside its group; callers use it only for i > 0.
-__device__ __forceinline__ float lane_mirror8(float v) {
-  const int t = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x12F, 0xF, 0xF, false);
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(t, 0x141, 0xF, 0xF, false));
 }
 
 __device__ __forceinline__ float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }   // times -i
@@ -433,20 +409,18 @@ struct K3Args {
   const float* inv_scale;  // [F][n_sel]
   const double* kz;        // [n_sel][kz_row(N)] signed kz / (2 pi) of the selected bins at q = 0..N/2, cycles per metre
   const double* z;         // [n_z]
-  const float* basis;      // [N][N] slot-major fixed real basis (FP32 kernel)
   const void* basis_hi;    // [N/8 slot groups][N x][8 slots] basis, 16-bit hi part (split kernels)
   const void* basis_lo;    // same layout, 16-bit lo part
   float* accum;            // [n_split][F][n_acc][n_z][N]
   int32_t N, n_z, n_sel, F, n_dt, n_xg, n_split, bins_per_split, zero_evanescent;
   // factored-transform kernels (k3_factored.hpp)
   const double* kz_ff;     // [n_sel][N / 16][16] signed kz / (2 pi) at q = (N / 16) q1 + r, stored at [r][q1]
-  const float* ff_w32;     // [64 lanes][16] 16-point DFT matrix, FP32 operand order
   const void* ff_w16;      // [64 lanes][2 k-steps][hi 8, lo 8] 16-point DFT matrix, 16-bit operand order
   const float2* ff_tw;     // [64 lanes][8] twiddles e^{2 pi i q2 x1 / N} of the lane's stage-1 outputs (/ 16 for FP16)
   const int32_t* ev_bin;   // [n_sel] 1 if the bin has evanescent lateral wavenumbers
   const float2* ff_tw2;    // [64 lanes][8] e^{2 pi i x' / 512} of the lane's stage-3 outputs (N = 512)
-  const float2* ff_tw_vec; // [16 x1][16 q2] e^{2 pi i q2 x1 / 256} (vector FFT kernel)
-  const float2* ff_tw2_vec; // [16 x2][16 j] e^{2 pi i (j + 16 x2) / 512} (vector FFT kernel, N = 512)
+  const float2* ff_tw_vec; // [16 x1][16 j] e^{2 pi i q2 x1 / 16 K}, q2 the column of lane j (vector FFT kernel)
+  const float2* ff_tw2_vec; // [16 x2][16 j] e^{2 pi i (j + 16 x2) / N} (vector FFT kernel, N > 256)
 };
 
 // Grouped work list of the factored fields kernels: frames of different record lengths

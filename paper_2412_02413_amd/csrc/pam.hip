@@ -105,11 +105,9 @@ struct pam_plan_s {
   float2* d_twx = nullptr;     // [N] lateral DFT twiddles
   float* d_masks = nullptr;    // [n_sub][L]
   int32_t col0 = 0, col_step = 1;  // grid column of element l: col0 + col_step * l
-  float* d_basis = nullptr;    // [N][N] slot-major cos/sin basis (FP32 kernel)
   uint16_t* d_bhi = nullptr;   // [N/8][N][8] basis (slot groups, x, slots), 16-bit hi (split kernels)
   uint16_t* d_blo = nullptr;   // same layout, 16-bit lo
-  bool ff = false;             // inverse lateral transform factored into two 16-point stages (N = 256, 512)
-  float* d_ff_w32 = nullptr;   // [64][16] 16-point DFT matrix in FP32 operand order
+  bool ff = false;             // factored inverse lateral transform: FP32, and the 16-bit forms at N = 256, 512
   uint16_t* d_ff_w16 = nullptr;  // [64][2][16] the same in 16-bit operand order, hi then lo per k-step
   float2* d_ff_tw = nullptr;   // [64][8] twiddles / 16 in stage-1 output order
   float2* d_ff_tw2 = nullptr;  // [64][8] N = 512 combination twiddles in stage-3 output order
@@ -219,15 +217,15 @@ LaunchShape k3_tiles(const pam_plan_s* p) {
   s.ct = 0;
   s.fw = 0;
   if (p->ff) {
-    // all columns per workgroup, ft_depths (vector FFT) depths per workgroup
+    // all columns per workgroup
     s.fw = -1;
     s.nw = pam::kFfWaves;
-    const int dpw = p->N == 512 ? pam::ft_depths<512>() : (p->N == 256 ? pam::ft_depths<256>() : pam::ft_depths<128>());
+    const int dpw = pam::ft_depths_of(p->N);     // k3ff's at N = 256 and 512 too
     s.n_dt = (p->n_z + dpw - 1) / dpw;
     s.n_xg = 1;
   } else if (p->N % 64 == 0) {
     // 16 depths x 64 ct columns per workgroup (4 consumer + 4 producer waves)
-    s.ct = p->N % 256 == 0 ? 4 : (p->N % 128 == 0 ? 2 : 1);
+    s.ct = p->N % 128 == 0 ? 2 : 1;
     s.nw = 4;
     s.n_dt = (p->n_z + 15) / 16;
     s.n_xg = p->N / (64 * s.ct);
@@ -249,10 +247,28 @@ int n_acc(int n_sub, int coherence = 0) { return n_sub == 3 ? 6 : (n_sub == 2 ? 
 // extra workgroups.  A group of F frames splits its bins at most 1 + spare / F ways, so its
 // accumulator region (F + spare planes) and with it the workspace size never shrink as F
 // grows: a workspace sized for F frames serves every call of fewer frames.
-int64_t k3_spare_planes(const pam_plan_s* p) {
+//
+// The FP32 plans at sizes other than 128, 256 and 512 have few, wide workgroups per frame and so reserve many
+// planes.  Where a caller's workspace (or the allocation-free entry point's scratch) does not hold that, the call
+// runs with a smaller reservation (full = false), sized as for workgroups of 16 x 64 pixels (16 x 128 at 384
+// columns, 32 x 32 where 64 does not divide N) on a device that holds 256 to 1,024 of them: its bins then split
+// fewer ways, and the results differ by the order of the FP32 sums.
+int64_t k3_spare_planes(const pam_plan_s* p, bool full = true) {
   const LaunchShape t = k3_tiles(p);
   const int64_t tiles = (int64_t)t.n_dt * t.n_xg;
-  return (2 * (int64_t)std::max(1, p->k3_slots) + tiles - 1) / tiles;
+  const int64_t spare = (2 * (int64_t)std::max(1, p->k3_slots) + tiles - 1) / tiles;
+  if (is_split(p->precision) || p->N == 128 || p->N == 256 || p->N == 512) return spare;
+  int64_t small_tiles, slots;
+  if (p->N % 64 == 0) {
+    const int cols = p->N % 128 == 0 ? 128 : 64;
+    small_tiles = (int64_t)((p->n_z + 15) / 16) * (p->N / cols);
+    slots = (cols == 64 ? 1280 : 1024) - 256 * p->n_sub;          // 1,024, 768, 512 or 768, 512, 256
+  } else {
+    small_tiles = (int64_t)((p->n_z + 31) / 32) * (p->N / 32);
+    slots = p->n_sub == 1 ? 1024 : 512;
+  }
+  const int64_t small = (2 * slots + small_tiles - 1) / small_tiles;
+  return full ? std::max(spare, small) : small;
 }
 
 // The bin split of a K3 launch over n groups of frames (F[g] frames of n_sel[g] bins).
@@ -265,10 +281,11 @@ int64_t k3_spare_planes(const pam_plan_s* p) {
 // per bin).  Returns the bins-per-workgroup cap b (every group splits into ceil(n_sel / b)
 // parts) that minimises the estimate, the largest such b on ties, at least 8 bins (or the
 // widest band when narrower), among the caps whose splits fit the spare planes.
-int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr) {
+int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr,
+               bool full = true) {
   const LaunchShape t = k3_tiles(p);
   const int64_t tiles = (int64_t)t.n_dt * t.n_xg;
-  const int64_t spare = k3_spare_planes(p);
+  const int64_t spare = k3_spare_planes(p, full);
   int max_n = 0;
   for (int g = 0; g < n; ++g) max_n = std::max(max_n, n_sel[g]);
   if (max_n == 0) {
@@ -348,10 +365,11 @@ const Level* level_for(const pam_plan_s* p, int n_t) {
 }
 
 // bin_cap: the bins-per-workgroup cap of the launch this group is part of (-1: the group alone)
-pam_status_t layout(const pam_plan_s* p, int64_t F, int n_t, pam_workspace_layout_t* out, int bin_cap = -1) {
+pam_status_t layout(const pam_plan_s* p, int64_t F, int n_t, pam_workspace_layout_t* out, int bin_cap = -1,
+                    bool full = true) {
   const Level* lv = level_for(p, n_t);
   if (!lv) return PAM_ERR_INVALID_ARG;
-  if (bin_cap < 0) bin_cap = k3_bin_cap(p, &F, &lv->n_sel, 1);
+  if (bin_cap < 0) bin_cap = k3_bin_cap(p, &F, &lv->n_sel, 1, nullptr, full);
   const LaunchShape s = k3_shape(p, lv->n_sel, bin_cap);
   const size_t pix = (size_t)p->n_z * p->N;
   const size_t n_blk = (pix + 255) / 256;
@@ -360,7 +378,7 @@ pam_status_t layout(const pam_plan_s* p, int64_t F, int n_t, pam_workspace_layou
   L.spectra = o;  o = align256(o + (size_t)F * lv->n_sel * p->L * sizeof(float2));
   L.coeffs = o;   o = align256(o + (size_t)F * lv->n_sel * p->n_sub * p->N * sizeof(float2));
   L.scales = o;   o = align256(o + (size_t)F * lv->n_sel * sizeof(float));
-  const size_t planes = F > 0 ? (size_t)F + (size_t)k3_spare_planes(p) : 0;   // >= n_split F
+  const size_t planes = F > 0 ? (size_t)F + (size_t)k3_spare_planes(p, full) : 0;   // >= n_split F
   L.accum = o;    o = align256(o + planes * n_acc(p->n_sub, p->coherence) * pix * sizeof(float));
   L.energy = o;   o = align256(o + (size_t)F * pix * sizeof(float));
   L.weight = o;   o = align256(o + (size_t)F * pix * sizeof(float));
@@ -406,8 +424,7 @@ hipError_t launch_prec(int precision, const pam::K3Args& a, int blocks, Target s
       return launch_with_lds(pam::k3_fields_split<__bf16, 1, NSUB, NC>, NC, pam::k3_split_lds<1, NSUB, NC>(), a, blocks, st);
     case PAM_PREC_FP16:
       return launch_with_lds(pam::k3_fields_split<_Float16, 1, NSUB, NC>, NC, pam::k3_split_lds<1, NSUB, NC>(), a, blocks, st);
-    default:
-      return launch_with_lds(pam::k3_fields_fp32<NSUB, NC>, NC, pam::k3_fp32_lds<NSUB, NC>(), a, blocks, st);
+    default: return hipErrorInvalidValue;          // FP32 takes the factored kernel at every N
   }
 }
 
@@ -422,8 +439,7 @@ hipError_t launch_prec16(int precision, const pam::K3Args& a, int blocks, Target
       return launch_with_lds(pam::k3f16_split<__bf16, 1, NSUB, CT>, 4, pam::k3f16_split_lds<1, NSUB, CT>(), a, blocks, st);
     case PAM_PREC_FP16:
       return launch_with_lds(pam::k3f16_split<_Float16, 1, NSUB, CT>, 4, pam::k3f16_split_lds<1, NSUB, CT>(), a, blocks, st);
-    default:
-      return launch_with_lds(pam::k3f16_fp32<NSUB, CT>, 4, pam::k3f16_fp32_lds<NSUB, CT>(), a, blocks, st);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -451,22 +467,23 @@ hipError_t launch_ff_r(int precision, const pam::K3Args& a, const pam::K3Groups&
     case PAM_PREC_SPLIT_FP16: return launch_big_lds(k3ff<_Float16, 3, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
     case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
     case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
-    default: return launch_big_lds(k3ff<float, 1, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
+    default: return hipErrorInvalidValue;
   }
+}
+
+// FP32 operands: the vector FFT kernel of the plan's lateral size.
+template <int NSUB, int NN = 32>
+hipError_t launch_fft(const pam::K3Args& a, const pam::K3Groups& grp, int blocks, Target st) {
+  if (a.N == NN)
+    return launch_big_lds(pam::k3fft<NSUB, false, NN>, pam::kFtWaves, pam::k3fft_lds<NSUB, NN>(),
+                          pam::k3fft_lds<NSUB, NN>(), a, grp, blocks, st);
+  if constexpr (NN < kMaxNx) return launch_fft<NSUB, NN + 32>(a, grp, blocks, st);
+  return hipErrorInvalidValue;
 }
 
 template <int NSUB>
 hipError_t launch_ff(int precision, const pam::K3Args& a, const pam::K3Groups& grp, int blocks, Target st) {
-  // FP32 operands: the vector FFT kernel (32, 16 or 8 depths per workgroup; 16 and 8 like k3ff)
-  if (precision == PAM_PREC_FP32 && a.N == 256)
-    return launch_big_lds(pam::k3fft<NSUB>, pam::kFtWaves, pam::k3fft_lds<NSUB>(), pam::k3fft_lds<NSUB>(), a, grp,
-                          blocks, st);
-  if (precision == PAM_PREC_FP32 && a.N == 512)
-    return launch_big_lds(pam::k3fft<NSUB, false, 512>, pam::kFtWaves, pam::k3fft_lds<NSUB, 512>(),
-                          pam::k3fft_lds<NSUB, 512>(), a, grp, blocks, st);
-  if (precision == PAM_PREC_FP32 && a.N == 128)
-    return launch_big_lds(pam::k3fft<NSUB, false, 128>, pam::kFtWaves, pam::k3fft_lds<NSUB, 128>(),
-                          pam::k3fft_lds<NSUB, 128>(), a, grp, blocks, st);
+  if (precision == PAM_PREC_FP32) return launch_fft<NSUB>(a, grp, blocks, st);
   return a.N == 512 ? launch_ff_r<NSUB, 2>(precision, a, grp, blocks, st)
                     : launch_ff_r<NSUB, 1>(precision, a, grp, blocks, st);
 }
@@ -476,12 +493,22 @@ hipError_t launch_shape(int precision, const LaunchShape& s, const pam::K3Args& 
                         int blocks, Target st) {
   if (s.fw < 0) return launch_ff<NSUB>(precision, a, grp, blocks, st);
   if (grp.n > 0) return hipErrorInvalidValue;      // grouped work lists run on the factored kernels only
-  if (s.ct == 4) return launch_prec16<NSUB, 4>(precision, a, blocks, st);
   if (s.ct == 2) return launch_prec16<NSUB, 2>(precision, a, blocks, st);
   if (s.ct == 1) return launch_prec16<NSUB, 1>(precision, a, blocks, st);
   if (s.nw == 4) return launch_prec<NSUB, 4>(precision, a, blocks, st);
   if (s.nw == 2) return launch_prec<NSUB, 2>(precision, a, blocks, st);
   return launch_prec<NSUB, 1>(precision, a, blocks, st);
+}
+
+// K2 of the factored plans: the lateral FFT kernel of the plan's size.
+template <int NSUB, int NN = 32>
+bool launch_k2(int n, dim3 grid, hipStream_t stream, const pam::K2Args& a) {
+  if (n == NN) {
+    hipLaunchKernelGGL((pam::k2_fft<NSUB, NN / 16>), grid, dim3(256), 0, stream, a);
+    return true;
+  }
+  if constexpr (NN < kMaxNx) return launch_k2<NSUB, NN + 32>(n, grid, stream, a);
+  return false;
 }
 
 hipError_t launch_k3(int precision, int n_sub, const LaunchShape& s, const pam::K3Args& a, const pam::K3Groups& grp,
@@ -599,10 +626,9 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
     const double a = 2.0 * kPi * (double)i / (double)N;
     twx[i] = make_float2((float)std::cos(a), (float)-std::sin(a));
   }
-  // Factored transform for N = 256 and 512 (k3_factored.hpp, and the vector FFT of k3_fft.hpp
-  // in FP32), and N = 128 in FP32 (k3_fft.hpp); the other cases take the folded DFT basis
-  // (k3_fields*.hpp), built only for them.
-  p->ff = (N == 256 || N == 512 || (N == 128 && p->precision == PAM_PREC_FP32));
+  // Factored transform: FP32 at every N (vector FFT, k3_fft.hpp) and the 16-bit forms at N = 256 and 512
+  // (k3_factored.hpp); the 16-bit forms' other sizes take the folded DFT basis (k3_fields*.hpp), built only for them.
+  p->ff = !is_split(p->precision) || N == 256 || N == 512;
   std::vector<float> basis(p->ff ? 0 : (size_t)N * N);
   for (int s = 0; s < (p->ff ? 0 : N); ++s) {
     const int q = s >> 1;
@@ -640,24 +666,20 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
   // odd q): the 16-point DFT matrix W(x, m) = e^{2 pi i m x / 16} in real form, rows
   // (x, re/im) = x + 16 ro, the stage twiddles and (N = 512) the combination twiddles, all
   // in lane order of the matrix-core operands.  Lane l: column c = l % 32, half h = l / 32.
-  std::vector<float> ff_w32;
   std::vector<uint16_t> ff_w16;
   std::vector<float2> ff_tw, ff_tw2, ff_tw_vec, ff_tw2_vec;
-  if (p->ff) {
+  if (p->ff && is_split(p->precision)) {
     auto wval = [](int row, int m, int ri) {
       const int x = row % 16, ro = row / 16;
       const double th = 2.0 * kPi * (double)((m * x) % 16) / 16.0;
       const double c = std::cos(th), sn = std::sin(th);
       return ro == 0 ? (ri == 0 ? c : -sn) : (ri == 0 ? sn : c);
     };
-    ff_w32.resize(64 * 16);
     ff_w16.resize(64 * 32);
     ff_tw.resize(64 * 8);
     const bool h16 = is_fp16(p->precision);
     for (int l = 0; l < 64; ++l) {
       const int c = l % 32, h = l / 32;
-      // FP32 k-step t: k = 2t + h <-> input m = 8h + t/2, re/im t%2
-      for (int t = 0; t < 16; ++t) ff_w32[l * 16 + t] = (float)wval(c, 8 * h + t / 2, t % 2);
       // 16-bit k-step s, element j: k = 16s + 8h + j <-> m = 8h + 4s + j/2, re/im j%2
       for (int s2 = 0; s2 < 2; ++s2)
         for (int j = 0; j < 8; ++j) {
@@ -675,23 +697,6 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
         ff_tw[l * 8 + v] = make_float2((float)(std::cos(th) * sc), (float)(std::sin(th) * sc));
       }
     }
-    // vector FFT kernel: [x1][j] = e^{2 pi i q2 x1 / N} with q2 = j (N = 256, 512) or j % 8 (N = 128)
-    ff_tw_vec.resize(256);
-    const int NT = N == 128 ? 128 : 256;
-    for (int x1 = 0; x1 < 16; ++x1)
-      for (int jj = 0; jj < 16; ++jj) {
-        const int q2 = N == 128 ? jj % 8 : jj;
-        const double th = 2.0 * kPi * (double)((q2 * x1) % NT) / (double)NT;
-        ff_tw_vec[x1 * 16 + jj] = make_float2((float)std::cos(th), (float)std::sin(th));
-      }
-    // vector FFT kernel, N = 512: [x2][j] = e^{2 pi i (j + 16 x2) / 512}
-    ff_tw2_vec.assign(256, make_float2(0.f, 0.f));
-    if (N == 512)
-      for (int x2 = 0; x2 < 16; ++x2)
-        for (int j = 0; j < 16; ++j) {
-          const double th = 2.0 * kPi * (double)(j + 16 * x2) / 512.0;
-          ff_tw2_vec[x2 * 16 + j] = make_float2((float)std::cos(th), (float)std::sin(th));
-        }
     // stage-3 output v of lane l is x' = c % 16 + 16 (8(v/4) + 4h + v%4) of half c / 16
     ff_tw2.assign(64 * 8, make_float2(0.f, 0.f));
     if (N == 512)
@@ -701,6 +706,20 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
           const double th = 2.0 * kPi * (double)xp / 512.0;
           ff_tw2[l * 8 + v] = make_float2((float)std::cos(th), (float)std::sin(th));
         }
+  } else if (p->ff) {
+    // vector FFT kernel: [x1][j] = e^{2 pi i q2 x1 / 16 K}, q2 = j % CW the stage-1 column of lane j (K of the CW
+    // lanes of a depth hold one, the others a zero) and, beyond N = 256, [x2][j] = e^{2 pi i (j + 16 x2) / N}
+    const int K = N > 256 ? N / 32 : N / 16, CW = K <= 2 ? 2 : (K <= 4 ? 4 : (K <= 8 ? 8 : 16));
+    ff_tw_vec.assign(256, make_float2(0.f, 0.f));
+    ff_tw2_vec.assign(256, make_float2(0.f, 0.f));
+    for (int x1 = 0; x1 < 16; ++x1)
+      for (int j = 0; j < 16; ++j) {
+        const int q2 = j % CW;
+        const double th = 2.0 * kPi * (double)(q2 * x1) / (double)(16 * K);
+        if (q2 < K) ff_tw_vec[x1 * 16 + j] = make_float2((float)std::cos(th), (float)std::sin(th));
+        const double th2 = 2.0 * kPi * (double)(j + 16 * x1) / (double)N;
+        if (N > 256) ff_tw2_vec[x1 * 16 + j] = make_float2((float)std::cos(th2), (float)std::sin(th2));
+      }
   }
 
   do {
@@ -708,11 +727,11 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
       if ((st = upload(p, &p->d_bhi, bhi.data(), bhi.size())) != PAM_OK) break;
       if ((st = upload(p, &p->d_blo, blo.data(), blo.size())) != PAM_OK) break;
     }
-    if (p->ff) {
-      if ((st = upload(p, &p->d_ff_w32, ff_w32.data(), ff_w32.size())) != PAM_OK) break;
+    if (p->ff && is_split(p->precision)) {
       if ((st = upload(p, &p->d_ff_w16, ff_w16.data(), ff_w16.size())) != PAM_OK) break;
       if ((st = upload(p, &p->d_ff_tw, ff_tw.data(), ff_tw.size())) != PAM_OK) break;
       if ((st = upload(p, &p->d_ff_tw2, ff_tw2.data(), ff_tw2.size())) != PAM_OK) break;
+    } else if (p->ff) {
       if ((st = upload(p, &p->d_ff_tw_vec, ff_tw_vec.data(), ff_tw_vec.size())) != PAM_OK) break;
       if ((st = upload(p, &p->d_ff_tw2_vec, ff_tw2_vec.data(), ff_tw2_vec.size())) != PAM_OK) break;
     }
@@ -727,7 +746,6 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
           if (masks[(size_t)i * L + l] != 0.f) subs[l] |= 1 << i;
       if ((st = upload(p, &p->d_subs, subs.data(), subs.size())) != PAM_OK) break;
     }
-    if (!p->ff && (st = upload(p, &p->d_basis, basis.data(), basis.size())) != PAM_OK) break;
     // bin subsets for records of n_t / 2^j samples
     for (int stride = 1; p->n_t / stride >= kMinSamples; stride <<= 1) {
       Level lv;
@@ -831,7 +849,7 @@ namespace {
 // group g's bins-per-workgroup cap, the shared one for a grouped launch, else the group's own.
 pam_status_t grouped_layout(const pam_plan_s* p, const pam_group_t* groups, int n_groups,
                             pam_workspace_layout_t* W, size_t* base, size_t* total,
-                            int* cap, bool* one_launch) {
+                            int* cap, bool* one_launch, bool full = true) {
   if (n_groups < 1 || n_groups > pam::kMaxGroups || !groups) return PAM_ERR_INVALID_ARG;
   int64_t F_total = 0;
   int64_t F[pam::kMaxGroups];
@@ -850,13 +868,13 @@ pam_status_t grouped_layout(const pam_plan_s* p, const pam_group_t* groups, int 
   double separate = 0;
   for (int g = 0; g < n_groups; ++g) {
     double c = 0;
-    cap[g] = k3_bin_cap(p, &F[g], &n_sel[g], 1, &c);
+    cap[g] = k3_bin_cap(p, &F[g], &n_sel[g], 1, &c, full);
     separate += c;
   }
   *one_launch = false;
   if (p->ff && live > 1) {
     double together = 0;
-    const int shared = k3_bin_cap(p, F, n_sel, n_groups, &together);
+    const int shared = k3_bin_cap(p, F, n_sel, n_groups, &together, full);
     if (together < separate) {
       *one_launch = true;
       for (int g = 0; g < n_groups; ++g) cap[g] = shared;
@@ -864,7 +882,7 @@ pam_status_t grouped_layout(const pam_plan_s* p, const pam_group_t* groups, int 
   }
   size_t o = 0;
   for (int g = 0; g < n_groups; ++g) {
-    const pam_status_t st = layout(p, groups[g].n_frames, groups[g].n_t, &W[g], cap[g]);
+    const pam_status_t st = layout(p, groups[g].n_frames, groups[g].n_t, &W[g], cap[g], full);
     if (st != PAM_OK) return st;
     base[g] = o;
     o = align256(o + W[g].total);
@@ -887,6 +905,8 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
   int cap[pam::kMaxGroups];
   bool one_launch = false;
   pam_status_t st = grouped_layout(p, groups, n_groups, W, wbase, &total, cap, &one_launch);
+  if (st == PAM_OK && workspace && ws_bytes < total)        // the smaller reservation, where the plan has one
+    st = grouped_layout(p, groups, n_groups, W, wbase, &total, cap, &one_launch, false);
   if (st != PAM_OK) return st;
   if (events && n_groups != 1) return PAM_ERR_INVALID_ARG;
   int64_t F_total = 0;
@@ -1006,18 +1026,9 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
     if (p->ff) {
       // factored order: the lateral FFT, one wave per (frame, bin)
       const dim3 grid((unsigned)((items + 3) / 4));
-      switch (p->N * 4 + p->n_sub) {
-        case 128 * 4 + 1: hipLaunchKernelGGL((pam::k2_fft<1, 8>), grid, dim3(256), 0, stream, a); break;
-        case 128 * 4 + 2: hipLaunchKernelGGL((pam::k2_fft<2, 8>), grid, dim3(256), 0, stream, a); break;
-        case 128 * 4 + 3: hipLaunchKernelGGL((pam::k2_fft<3, 8>), grid, dim3(256), 0, stream, a); break;
-        case 256 * 4 + 1: hipLaunchKernelGGL((pam::k2_fft<1, 16>), grid, dim3(256), 0, stream, a); break;
-        case 256 * 4 + 2: hipLaunchKernelGGL((pam::k2_fft<2, 16>), grid, dim3(256), 0, stream, a); break;
-        case 256 * 4 + 3: hipLaunchKernelGGL((pam::k2_fft<3, 16>), grid, dim3(256), 0, stream, a); break;
-        case 512 * 4 + 1: hipLaunchKernelGGL((pam::k2_fft<1, 32>), grid, dim3(256), 0, stream, a); break;
-        case 512 * 4 + 2: hipLaunchKernelGGL((pam::k2_fft<2, 32>), grid, dim3(256), 0, stream, a); break;
-        case 512 * 4 + 3: hipLaunchKernelGGL((pam::k2_fft<3, 32>), grid, dim3(256), 0, stream, a); break;
-        default: return PAM_ERR_UNSUPPORTED;
-      }
+      const bool known = p->n_sub == 3 ? launch_k2<3>(p->N, grid, stream, a)
+                                       : (p->n_sub == 2 ? launch_k2<2>(p->N, grid, stream, a) : launch_k2<1>(p->N, grid, stream, a));
+      if (!known) return PAM_ERR_UNSUPPORTED;
     } else {
       const size_t lds = (size_t)(p->N + 3 * p->L + 2 * p->n_sub * p->N) * sizeof(float2);
       if (p->n_sub == 3)
@@ -1031,9 +1042,9 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
     return PAM_OK;
   };
   auto args_for = [&](const G& q) {
-    return pam::K3Args{q.coeffs, q.scales, q.lv->d_kz, p->d_z, p->d_basis, p->d_bhi, p->d_blo, q.accum,
+    return pam::K3Args{q.coeffs, q.scales, q.lv->d_kz, p->d_z, p->d_bhi, p->d_blo, q.accum,
                        p->N, p->n_z, q.lv->n_sel, q.F, q.s.n_dt, q.s.n_xg, q.s.n_split, q.s.bins_per_split,
-                       p->zero_evanescent, q.lv->d_kzff, p->d_ff_w32, p->d_ff_w16, p->d_ff_tw, q.lv->d_ev,
+                       p->zero_evanescent, q.lv->d_kzff, p->d_ff_w16, p->d_ff_tw, q.lv->d_ev,
                        p->d_ff_tw2, p->d_ff_tw_vec, p->d_ff_tw2_vec};
   };
   // K3: the fields and cross-spectra sums of one group (frequency-domain delay-and-sum for method 1,
@@ -1245,6 +1256,8 @@ pam_status_t pam_as_tax_noalloc(pam_plan_t p, const float* rf, int64_t n_frames,
   if (!p || n_frames < 0) return PAM_ERR_INVALID_ARG;
   pam_workspace_layout_t W;
   pam_status_t st = layout(p, n_frames, n_t, &W);
+  if (st != PAM_OK) return st;
+  if (W.total > (size_t)PAM_NOALLOC_SCRATCH_BYTES) st = layout(p, n_frames, n_t, &W, -1, false);
   if (st != PAM_OK) return st;
   if (W.total > (size_t)PAM_NOALLOC_SCRATCH_BYTES) return PAM_ERR_WORKSPACE;
   if (n_frames == 0) return PAM_OK;

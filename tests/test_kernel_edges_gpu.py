@@ -2,6 +2,7 @@
 import numpy as np
 import pytest
 
+from oracle import as_tax as O
 from paper_2412_02413_amd import synth
 
 
@@ -141,3 +142,71 @@ def test_weight_and_energy_from_partial_sums(env, n_sub, eps, frames):
     print(f"{lay.n_split} splits, smallest weight {w.min():.1e}", flush=True)
     np.testing.assert_allclose(view(lay.weight, frames * pix).reshape(frames, pix), w, rtol=2.0 ** -23)
     np.testing.assert_allclose(view(lay.energy, frames * pix).reshape(frames, pix), E, rtol=2.0 ** -23)
+
+
+MM = 1e-3
+
+
+def lateral_case(n_x, n_sub, n_depths, **kw):
+    """A small array on n_x columns: 52 bins, 5 of them with evanescent wavenumbers in range."""
+    L = min(32, n_x)
+    g = synth.Geometry(n_elements=L, pitch_m=0.3 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=256,
+                       bands_hz=[(2e6, 6e6)], depths_m=(15 + 0.4 * np.arange(n_depths)) * MM, n_x=n_x, n_sub=n_sub,
+                       pattern_m=4).replace(**kw)
+    rng = np.random.default_rng(n_x + n_sub)
+    em = [synth.Emitter(-1.0 * MM, 19 * MM, "broadband"), synth.Emitter(2.0 * MM, 24 * MM, "broadband")]
+    return g, synth.render(g, em, rng, snr_db=20.0)
+
+
+# The tolerances of the FP32 path everywhere: image 1e-5 relative, NNCC 1e-4 absolute.
+@pytest.mark.parametrize("n_x", list(range(32, 513, 32)))
+@pytest.mark.parametrize("n_sub", [1, 2, 3])
+def test_every_lateral_size(env, n_x, n_sub):
+    """The vector FFT kernels (lateral and fields) at every size, against the oracle: a depth count
+    that leaves a ragged last tile, padded columns; zero-stuffed ones where 32 divides n_x."""
+    torch, _ = env
+    from paper_2412_02413_amd import pam
+    for kw in ({}, {"lateral": "stuff", "evanescent": "zero"}):
+        g, rf = lateral_case(n_x, n_sub, 19, **kw)
+        plan = pam.pam_plan(g, 0, "fp32")
+        try:
+            out = pam.reconstruct(plan, torch.from_numpy(rf[None]).cuda())
+            torch.cuda.synchronize()
+        finally:
+            pam.pam_destroy(plan)
+        ref = O.as_tax(rf, g)
+        e_i = rel(out["image"][0].double().cpu().numpy(), ref["I"])
+        e_r = float(np.abs(out["nncc"][0].double().cpu().numpy() - ref["rho_n"]).max())
+        print(f"{n_x} {n_sub} {kw}: image {e_i:.1e} nncc {e_r:.1e}", flush=True)
+        assert e_i <= 1e-5 and e_r <= 1e-4
+
+
+@pytest.mark.parametrize("n_x", [96, 192, 384])
+def test_smaller_reservation_of_partial_sums(env, n_x):
+    """A call whose workspace lacks the full reservation of partial-sum planes splits its bins fewer
+    ways: the same results up to the order of FP32 sums; one byte less than that still fails."""
+    torch, _ = env
+    from paper_2412_02413_amd import pam
+    g, rf = lateral_case(n_x, 3, 64)
+    plan = pam.pam_plan(g, 0, "fp32")
+    try:
+        x = torch.from_numpy(rf[None]).cuda()
+        want = pam.reconstruct(plan, x)["image"].clone()
+        img = torch.empty_like(want)
+        lay = pam.pam_workspace_layout(plan, 1, g.n_samples)
+        plane = 4 * 6 * g.n_z * g.n_x
+        fits, lo, hi = lay.total, lay.total - (lay.energy - lay.accum) + plane, lay.total
+        while hi - lo > 256:                                  # smallest accepted size, to 256 bytes
+            mid = (lo + hi) // 512 * 256
+            ws = torch.empty(mid, dtype=torch.uint8, device="cuda")
+            try:
+                pam.pam_as_tax(plan, x, img, None, None, ws)
+                assert rel(img.double().cpu().numpy(), want.double().cpu().numpy()) < 1e-6, mid
+                fits = hi = mid
+            except pam.PamError as e:
+                assert e.status == pam.PAM_ERR_WORKSPACE
+                lo = mid
+        print(f"{n_x}: {lay.total} bytes reserved, {fits} accepted", flush=True)
+        assert fits < lay.total
+    finally:
+        pam.pam_destroy(plan)
