@@ -8,112 +8,231 @@
 // sums over w of |p_i|^2 and Re(p_i^* p_j) then give the NCC, TAX weight and image
 // exactly as for the angular-spectrum fields (K4).
 //
-// One thread per pixel.  Bins run in chunks of TEA_BC: the chunk's element spectra
-// are staged in LDS (read by every thread, broadcast), and for each element the
-// thread forms its distance to the pixel in FP64, the phase k u (u = distance fs /
-// (n_t c), cycles per bin index) in FP64 reduced to [-1/2, 1/2] cycle, and the
-// hardware sine and cosine; the advanced spectrum is added to the field of every
-// sub-aperture that holds the element (a per-element bit set, uniform over the
-// workgroup).  After the chunk the fields are folded into the six per-pixel sums.
-// No delay table is stored: an FP32 table would leave phase errors of ~2e-5 cycle at
-// 8 MHz, and the FP64 distance costs a few instructions per element and chunk.
+// Elements sit on grid columns (col0 + step l), so the phasor depends on a pixel column x
+// and an element only through x - step l: with x = r + step t (r < step), the pixels of one
+// depth and residue r form a Toeplitz product over D = t - l.  Its T + L - 1 phasors are
+// made once per (depth, residue, bin) - phase k u in FP64 (u = distance fs / (n_t c), cycles
+// per bin index) reduced to [-1/2, 1/2] cycle, hardware sine and cosine - instead of once per
+// (pixel, element, bin), and what remains is four FMAs per (pixel, element, bin): the vector
+// FMA rate is the bound.
+//
+// Work split.  A lane holds four consecutive pixels t = 4 q .. 4 q + 3, so four elements
+// need seven phasors per lane, three of them left from the four before: four 8-byte LDS reads
+// per 64 FMAs.  Elements run in units of eight.  The table is stored as four planes (D mod 4), so that lanes
+// of consecutive q read consecutive values.  The element spectra are uniform over the
+// workgroup and come through scalar loads; the sub-aperture of a unit is a scalar branch.  A
+// wave covers 64 lanes' worth of (depth, residue) rows (several where a row has few pixels,
+// part of one where it has more than 256) with its own table, so there is no workgroup
+// barrier.  u is kept beside the table in FP64: an FP32 delay would leave phase errors of
+// ~2e-5 cycle at 8 MHz.
+//
+// One frame of 512 x 256 pixels, 128 elements and 768 bins: 7.3 ms with one thread a pixel making every
+// (pixel, element, bin) phasor, 1.58 ms here (66 TFLOP/s of the 78.6 of unpacked vector FMAs; spectra and sub-aperture
+// sets through vector loads instead of scalar ones: 1.9 ms).
 #pragma once
 #include "kernels.hpp"
 
 namespace pam {
 
-constexpr int TEA_BC = 8;          // bins per chunk
-constexpr int TEA_THREADS = 256;   // pixels per workgroup
+constexpr int TEA_WAVES = 4;       // waves per workgroup
+constexpr int TEA_PX = 4;          // pixels per lane
 
 struct TeaArgs {
   const float2* spectra;   // [F][n_sel][L] (K1)
   const int32_t* ksel;     // [n_sel] bin index k on the call's record-length grid
-  const int32_t* subs;     // [L] bit i set if sub-aperture i holds element l
+  const int32_t* units;    // [(L + 7) / 8] unit codes
   const double* z;         // [n_z] depths
   float* accum;            // [n_split][F][n_acc][n_z][N]
-  double x_first;          // lateral coordinate of grid column 0
   double dx;               // grid spacing
-  double xl_first;         // lateral coordinate of element 0
-  double pitch;            // element pitch
   double cyc;              // fs / (n_t c): phase cycles per bin index per metre of path
-  int32_t L, N, n_z, n_sel, F, n_split, bins_per_split, n_ptile;
+  int32_t L, N, n_z, n_sel, F, n_split, bins_per_split;
+  int32_t col0, step;      // grid column of element l: col0 + step l
+  // the split of a depth's pixels into lanes (tea_shape)
+  int32_t T, Q, rows, chunks, PL, n_wg;
 };
 
-template <int NSUB>
-__global__ __launch_bounds__(TEA_THREADS) void k3_tea(TeaArgs a) {
+// T pixels per (depth, residue) row; Q lanes of four pixels a row (at most 64) and `chunks` such pieces a row;
+// `rows` rows per wave; PL values per plane of a row's phasor table; n_wg workgroups per frame and bin split.
+inline void tea_shape(TeaArgs& a) {
+  a.T = (a.N + a.step - 1) / a.step;
+  const int q = (a.T + TEA_PX - 1) / TEA_PX;
+  a.Q = q < 64 ? q : 64;
+  a.chunks = (q + 63) / 64;
+  a.rows = 64 / a.Q;
+  a.PL = a.Q + 2 * ((a.L + 7) / 8);
+  const long long waves = ((long long)a.n_z * a.step + a.rows - 1) / a.rows * a.chunks;
+  a.n_wg = (int)((waves + TEA_WAVES - 1) / TEA_WAVES);
+}
+// bytes of LDS per workgroup: u (FP64) and the phasors of every wave's rows (at most 48 KiB, 512 elements on 512
+// columns)
+inline size_t tea_lds(const TeaArgs& a) { return (size_t)TEA_WAVES * a.rows * 4 * a.PL * (sizeof(double) + sizeof(float2)); }
+
+// Element j of four times the four pixels' phasors w[3 + i - j], the seven of them split as lo = w[0..3] and
+// hi = w[4..6].
+__device__ __forceinline__ void tea_mac(float2 (&p)[TEA_PX], float2 x, int j, const float2 (&lo)[4], const float2 (&hi)[4]) {
+#pragma unroll
+  for (int i = 0; i < TEA_PX; ++i) {
+    const float2 e = 3 + i - j < 4 ? lo[(3 + i - j) & 3] : hi[(3 + i - j) & 3];
+    p[i].x = fmaf(x.x, e.x, fmaf(-x.y, e.y, p[i].x));
+    p[i].y = fmaf(x.x, e.y, fmaf(x.y, e.x, p[i].y));
+  }
+}
+
+// The spectra of a unit's eight elements, uniform over the workgroup and read through the scalar cache (the constant
+// address space; nothing writes them while the kernel runs).  The last unit of a bin may read up to seven values past
+// it: the next bin's, or after the last bin the workspace region that follows the spectra.
+typedef float __attribute__((address_space(4))) scalar_float;
+typedef int32_t __attribute__((address_space(4))) scalar_int;
+__device__ __forceinline__ void tea_load(float (&x)[16], const scalar_float* X) {
+#pragma unroll
+  for (int j = 0; j < 16; ++j) x[j] = X[j];
+}
+
+// Unit codes (tea_unit_code on the host): bits 24 and up name the sub-aperture that alone holds all eight elements, or
+// kTeaNone or kTeaMixed; bits 3 j + i say whether element j is in sub-aperture i.  Elements past the last are in none.
+constexpr int kTeaNone = 3, kTeaMixed = 4;
+inline int tea_unit_code(const int* sets, int n) {    // the sets (bit i: in sub-aperture i) of the unit's n elements
+  int code = 0;
+  bool same = true;
+  for (int j = 0; j < 8; ++j) {
+    const int b = j < n ? sets[j] : 0;
+    code |= b << (3 * j);
+    same = same && b == sets[0];
+  }
+  const int one = !same ? kTeaMixed : (sets[0] == 0 ? kTeaNone : (sets[0] == 1 ? 0 : (sets[0] == 2 ? 1 : (sets[0] == 4 ? 2 : kTeaMixed))));
+  return code | one << 24;
+}
+
+// MIXED: some unit belongs to more than one sub-aperture (the plan knows), so the loop has the branch per element
+template <int NSUB, bool MIXED>
+__global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
   constexpr int NP = AccCount<NSUB>::pairs;
-  extern __shared__ float2 xs[];                  // [TEA_BC][L]
-  __shared__ int ks[TEA_BC];
+  extern __shared__ double lds_tea[];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int bid = blockIdx.x;
   const int sp = bid % a.n_split; bid /= a.n_split;
-  const int pt = bid % a.n_ptile; bid /= a.n_ptile;
+  const int wg = bid % a.n_wg; bid /= a.n_wg;
   const int f = bid;
   const int b_begin = sp * a.bins_per_split;
   const int b_end = min(a.n_sel, b_begin + a.bins_per_split);
-  const int pix = pt * TEA_THREADS + threadIdx.x;
-  const int npix = a.n_z * a.N;
-  const bool live = pix < npix;
-  const int d = live ? pix / a.N : 0, j = live ? pix - (pix / a.N) * a.N : 0;
-  const double z = a.z[d];
-  const double x = a.x_first + j * a.dx;
+  const int units = (a.L + 7) / 8, entries = 4 * a.PL;              // units of eight elements; phasors of a row
+  const scalar_int* codes = (const scalar_int*)a.units;
+  const int wave = wg * TEA_WAVES + w, chunk = wave % a.chunks;
+  const int row0 = wave / a.chunks * a.rows, n_rows = a.n_z * a.step;   // (depth, residue) rows of this wave
+  double* u = lds_tea + (size_t)w * a.rows * entries;
+  float2* E = reinterpret_cast<float2*>(lds_tea + (size_t)TEA_WAVES * a.rows * entries) + (size_t)w * a.rows * entries;
 
-  float accS[NSUB], accC[NP > 0 ? NP : 1];
-#pragma unroll
-  for (int i = 0; i < NSUB; ++i) accS[i] = 0.f;
-#pragma unroll
-  for (int p = 0; p < (NP > 0 ? NP : 1); ++p) accC[p] = 0.f;
+  // plane p, position n of a row: D = 4 n + p - (8 units - 1) + first pixel of the chunk
+  for (int s = lane; s < a.rows * entries; s += 64) {
+    const int row = row0 + s / entries, e = s % entries;
+    const int D = 4 * (e % a.PL) + e / a.PL - (8 * units - 1) + 64 * TEA_PX * chunk;
+    const double z = row < n_rows ? a.z[row / a.step] : 0.0;
+    const double x = (double)(row % a.step - a.col0 + a.step * D) * a.dx;
+    u[s] = sqrt(x * x + z * z) * a.cyc;
+  }
 
-  for (int b0 = b_begin; b0 < b_end; b0 += TEA_BC) {
-    const int nb = min(TEA_BC, b_end - b0);
-    __syncthreads();
-    const float2* src = a.spectra + ((size_t)f * a.n_sel + b0) * a.L;
-    for (int e = threadIdx.x; e < nb * a.L; e += TEA_THREADS) xs[e] = src[e];
-    if ((int)threadIdx.x < nb) ks[threadIdx.x] = a.ksel[b0 + threadIdx.x];
-    __syncthreads();
-    float2 p[NSUB][TEA_BC];
+  const int slot = lane / a.Q;                                      // lanes past the wave's rows repeat row 0
+  const bool lane_live = slot < a.rows && row0 + slot < n_rows;
+  const int q = lane % a.Q;
+  const int t0 = TEA_PX * (64 * chunk + q);
+  const float2* Eq = E + (lane_live ? slot : 0) * entries + q;
+
+  float accS[NSUB][TEA_PX], accC[NP > 0 ? NP : 1][TEA_PX];
 #pragma unroll
-    for (int i = 0; i < NSUB; ++i)
+  for (int i = 0; i < TEA_PX; ++i) {
 #pragma unroll
-      for (int c = 0; c < TEA_BC; ++c) p[i][c] = make_float2(0.f, 0.f);
-    for (int l = 0; l < a.L; ++l) {
-      const int bits = __builtin_amdgcn_readfirstlane(a.subs[l]);
-      if (bits == 0) continue;
-      const double ddx = x - (a.xl_first + l * a.pitch);
-      const double u = sqrt(ddx * ddx + z * z) * a.cyc;      // cycles per bin index
+    for (int s = 0; s < NSUB; ++s) accS[s][i] = 0.f;
 #pragma unroll
-      for (int c = 0; c < TEA_BC; ++c) {
-        if (c < nb) {
-          const double ph = (double)ks[c] * u;
-          const float r = (float)(ph - rint(ph));
-          const float2 e = make_float2(__builtin_amdgcn_cosf(r), __builtin_amdgcn_sinf(r));
-          const float2 v = cmul(xs[c * a.L + l], e);
+    for (int c = 0; c < (NP > 0 ? NP : 1); ++c) accC[c][i] = 0.f;
+  }
+
+  for (int b = b_begin; b < b_end; ++b) {
+    const double k = (double)a.ksel[b];
+    for (int s = lane; s < a.rows * entries; s += 64) {
+      const double ph = k * u[s];
+      const float r = (float)(ph - rint(ph));
+      E[s] = make_float2(__builtin_amdgcn_cosf(r), __builtin_amdgcn_sinf(r));
+    }
+    __builtin_amdgcn_wave_barrier();
+    const scalar_float* X = (const scalar_float*)(a.spectra + ((size_t)f * a.n_sel + b) * a.L);
+    float2 p[NSUB][TEA_PX];
 #pragma unroll
-          for (int i = 0; i < NSUB; ++i)
-            if (bits & (1 << i)) p[i][c] = cadd(p[i][c], v);
+    for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+      for (int i = 0; i < TEA_PX; ++i) p[s][i] = make_float2(0.f, 0.f);
+    float x[16], xn[16];                                            // this unit's spectra, the next one's
+    tea_load(x, X);
+    auto unit = [&](int un, auto&& mac) {                           // mac(j, x_j, lo, hi) for the unit's elements
+      tea_load(xn, X + 16 * min(un + 1, units - 1));                // in flight during this unit's products
+      const float2* Ep = Eq + 2 * (units - 1 - un);
+      float2 e0[4], e1[4], e2[4];                                   // positions q + B, q + B + 1, q + B + 2
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        e0[c] = Ep[c * a.PL];
+        e1[c] = Ep[c * a.PL + 1];
+        e2[c] = c < 3 ? Ep[c * a.PL + 2] : e1[c];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mac(j, j, make_float2(x[2 * j], x[2 * j + 1]), e1, e2);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mac(4 + j, j, make_float2(x[8 + 2 * j], x[8 + 2 * j + 1]), e0, e1);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) x[j] = xn[j];
+    };
+    for (int un = 0; un < units;) {
+      const int code = codes[un];
+      if (MIXED && (code >> 24) == kTeaMixed) {
+        unit(un, [&](int j8, int j, float2 xj, const float2 (&lo)[4], const float2 (&hi)[4]) {
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s)
+            if (code >> (3 * j8 + s) & 1) tea_mac(p[s], xj, j, lo, hi);
+        });
+        ++un;
+        continue;
+      }
+      bool done = false;
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+        if ((code >> 24) == s) {                                    // a run of units that sub-aperture s alone holds
+          do {
+            unit(un, [&](int, int j, float2 xj, const float2 (&lo)[4], const float2 (&hi)[4]) {
+              tea_mac(p[s], xj, j, lo, hi);
+            });
+          } while (++un < units && codes[un] >> 24 == s);
+          done = true;
         }
+      if (!done) {                                                  // no sub-aperture holds any of the eight
+        ++un;
+        tea_load(x, X + 16 * min(un, units - 1));
       }
     }
+    __builtin_amdgcn_wave_barrier();                                // the table is free for the next bin
 #pragma unroll
-    for (int c = 0; c < TEA_BC; ++c) {
+    for (int i = 0; i < TEA_PX; ++i) {
 #pragma unroll
-      for (int i = 0; i < NSUB; ++i) accS[i] = fmaf(p[i][c].x, p[i][c].x, fmaf(p[i][c].y, p[i][c].y, accS[i]));
+      for (int s = 0; s < NSUB; ++s) accS[s][i] = fmaf(p[s][i].x, p[s][i].x, fmaf(p[s][i].y, p[s][i].y, accS[s][i]));
       if constexpr (NSUB == 3) {
-        accC[0] = fmaf(p[0][c].x, p[1][c].x, fmaf(p[0][c].y, p[1][c].y, accC[0]));
-        accC[1] = fmaf(p[1][c].x, p[2][c].x, fmaf(p[1][c].y, p[2][c].y, accC[1]));
-        accC[2] = fmaf(p[2][c].x, p[0][c].x, fmaf(p[2][c].y, p[0][c].y, accC[2]));
+        accC[0][i] = fmaf(p[0][i].x, p[1][i].x, fmaf(p[0][i].y, p[1][i].y, accC[0][i]));
+        accC[1][i] = fmaf(p[1][i].x, p[2][i].x, fmaf(p[1][i].y, p[2][i].y, accC[1][i]));
+        accC[2][i] = fmaf(p[2][i].x, p[0][i].x, fmaf(p[2][i].y, p[0][i].y, accC[2][i]));
       } else if constexpr (NSUB == 2) {
-        accC[0] = fmaf(p[0][c].x, p[1][c].x, fmaf(p[0][c].y, p[1][c].y, accC[0]));
+        accC[0][i] = fmaf(p[0][i].x, p[1][i].x, fmaf(p[0][i].y, p[1][i].y, accC[0][i]));
       }
     }
   }
-  if (!live) return;
+  if (!lane_live) return;
   constexpr int NA = AccCount<NSUB>::total;
-  const size_t plane = (size_t)npix;
-  float* dst = a.accum + ((size_t)sp * a.F + f) * NA * plane + pix;
+  const size_t plane = (size_t)a.n_z * a.N;
+  const int row = row0 + slot;
+  float* dst = a.accum + ((size_t)sp * a.F + f) * NA * plane + (size_t)(row / a.step) * a.N + row % a.step;
 #pragma unroll
-  for (int i = 0; i < NSUB; ++i) dst[i * plane] = accS[i];
+  for (int i = 0; i < TEA_PX; ++i) {
+    if (t0 + i >= a.T || row % a.step + a.step * (t0 + i) >= a.N) continue;
 #pragma unroll
-  for (int q = 0; q < NP; ++q) dst[(NSUB + q) * plane] = accC[q];
+    for (int s = 0; s < NSUB; ++s) dst[s * plane + a.step * (t0 + i)] = accS[s][i];
+#pragma unroll
+    for (int c = 0; c < NP; ++c) dst[(NSUB + c) * plane + a.step * (t0 + i)] = accC[c][i];
+  }
 }
 
 }  // namespace pam

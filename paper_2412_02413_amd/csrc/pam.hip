@@ -115,9 +115,9 @@ struct pam_plan_s {
   float2* d_ff_tw2_vec = nullptr;  // [16][16] N = 512 combination twiddles of the vector FFT kernel
   // frequency-domain delay-and-sum (pam_fd_tea_tax)
   double fs = 0, c = 0;        // sampling rate, sound speed
-  double dx = 0, x_first = 0;  // lateral grid spacing and coordinate of column 0
-  double xl_first = 0, pitch = 0;  // coordinate of element 0 and element pitch
-  int32_t* d_subs = nullptr;   // [L] bit i set if sub-aperture i holds element l
+  double dx = 0;               // lateral grid spacing
+  int32_t* d_units = nullptr;  // [(L + 7) / 8] sub-aperture sets of eight elements (tea_unit_code)
+  bool mixed_units = false;    // some of the eight belong to different sets
   int k3_slots = 512;          // K3 workgroups resident on the device at once
   int n_cus = 256;             // compute units of the plan's device
   std::vector<void*> allocs;
@@ -586,16 +586,9 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
     p->col_step = N / L;
     dx = g->pitch_m / p->col_step;
   }
-  // element and pixel coordinates (array centre at x = 0)
-  {
-    const double centre = p->col0 + p->col_step * (L - 1) / 2.0;
-    p->fs = g->fs_hz;
-    p->c = g->c_mps;
-    p->dx = dx;
-    p->x_first = -centre * dx;
-    p->xl_first = (p->col0 - centre) * dx;
-    p->pitch = p->col_step * dx;
-  }
+  p->fs = g->fs_hz;
+  p->c = g->c_mps;
+  p->dx = dx;
   // apodization masks: explicit or Pattern-m (a_i[l] = 1 iff floor(l/m) mod n == i)
   std::vector<float> masks((size_t)p->n_sub * L, 0.f);
   const int m = g->pattern_m > 0 ? g->pattern_m : 16;
@@ -744,7 +737,10 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
       for (int i = 0; i < p->n_sub; ++i)
         for (int l = 0; l < L; ++l)
           if (masks[(size_t)i * L + l] != 0.f) subs[l] |= 1 << i;
-      if ((st = upload(p, &p->d_subs, subs.data(), subs.size())) != PAM_OK) break;
+      std::vector<int32_t> units;
+      for (int l = 0; l < L; l += 8) units.push_back(pam::tea_unit_code(subs.data() + l, std::min(8, L - l)));
+      for (int32_t c : units) p->mixed_units |= (c >> 24) == pam::kTeaMixed;
+      if ((st = upload(p, &p->d_units, units.data(), units.size())) != PAM_OK) break;
     }
     // bin subsets for records of n_t / 2^j samples
     for (int stride = 1; p->n_t / stride >= kMinSamples; stride <<= 1) {
@@ -1052,18 +1048,37 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
   auto stage_k3 = [&](const G& q) -> pam_status_t {
     if (q.F == 0) return PAM_OK;
     if (method == 1) {
-      pam::TeaArgs a{q.spectra, q.lv->d_ksel, p->d_subs, p->d_z, q.accum, p->x_first, p->dx, p->xl_first, p->pitch,
-                     p->fs / ((double)q.n_t * p->c), p->L, p->N, p->n_z, q.lv->n_sel, q.F, q.s.n_split,
-                     q.s.bins_per_split, (pix + pam::TEA_THREADS - 1) / pam::TEA_THREADS};
-      const long long blocks = (long long)q.F * a.n_ptile * q.s.n_split;
+      pam::TeaArgs a{};
+      a.spectra = q.spectra;
+      a.ksel = q.lv->d_ksel;
+      a.units = p->d_units;
+      a.z = p->d_z;
+      a.accum = q.accum;
+      a.dx = p->dx;
+      a.cyc = p->fs / ((double)q.n_t * p->c);
+      a.L = p->L;
+      a.N = p->N;
+      a.n_z = p->n_z;
+      a.n_sel = q.lv->n_sel;
+      a.F = q.F;
+      a.n_split = q.s.n_split;
+      a.bins_per_split = q.s.bins_per_split;
+      a.col0 = p->col0;
+      a.step = p->col_step;
+      pam::tea_shape(a);
+      const long long blocks = (long long)q.F * a.n_wg * q.s.n_split;
       if (blocks > 0x7fffffffLL) return PAM_ERR_UNSUPPORTED;
-      const size_t lds = (size_t)pam::TEA_BC * p->L * sizeof(float2);
-      if (p->n_sub == 3)
-        hipLaunchKernelGGL(pam::k3_tea<3>, dim3((unsigned)blocks), dim3(pam::TEA_THREADS), lds, stream, a);
-      else if (p->n_sub == 2)
-        hipLaunchKernelGGL(pam::k3_tea<2>, dim3((unsigned)blocks), dim3(pam::TEA_THREADS), lds, stream, a);
-      else
-        hipLaunchKernelGGL(pam::k3_tea<1>, dim3((unsigned)blocks), dim3(pam::TEA_THREADS), lds, stream, a);
+      const size_t lds = pam::tea_lds(a);
+      const dim3 grid((unsigned)blocks), block(64 * pam::TEA_WAVES);
+      auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, stream, a); };
+      switch (2 * p->n_sub + p->mixed_units) {
+        case 7: launch(pam::k3_tea<3, true>); break;
+        case 6: launch(pam::k3_tea<3, false>); break;
+        case 5: launch(pam::k3_tea<2, true>); break;
+        case 4: launch(pam::k3_tea<2, false>); break;
+        case 3: launch(pam::k3_tea<1, true>); break;
+        default: launch(pam::k3_tea<1, false>); break;
+      }
       if (hipGetLastError() != hipSuccess) return PAM_ERR_DEVICE;
       return PAM_OK;
     }

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 from oracle import as_tax as O
+from oracle import fd_tea as T
 from paper_2412_02413_amd import synth
 
 
@@ -210,3 +211,42 @@ def test_smaller_reservation_of_partial_sums(env, n_x):
         assert fits < lay.total
     finally:
         pam.pam_destroy(plan)
+
+
+@pytest.mark.parametrize("L,n_x,n_sub,kw", [
+    (1, 32, 1, {}),                                        # one element, eight rows of pixels per wave
+    (13, 32, 3, {"pattern_m": 3}),                         # units of eight that mix sub-apertures, a ragged last one
+    (48, 96, 3, {"lateral": "stuff"}),                     # rows of 48 pixels, 12 lanes each
+    (32, 128, 2, {"lateral": "stuff", "pattern_m": 8}),    # four residues a column step
+    (9, 288, 3, {"lateral": "stuff", "pattern_m": 1}),     # 32 residues of nine pixels: ragged lanes
+    (160, 480, 3, {"pattern_m": 8}),                       # more than 64 lanes a row: two waves per depth
+    (512, 512, 3, {"pattern_m": 16}),                      # the largest phasor table
+    (40, 64, 3, {"overlap": True}),                        # elements in several sub-apertures and in none
+])
+def test_fd_tea_shapes(env, L, n_x, n_sub, kw):
+    """FD-TEA-TAX at the edges of its split of pixels into lanes and of elements into units of eight."""
+    torch, _ = env
+    from paper_2412_02413_amd import pam
+    overlap = "overlap" in kw
+    apod = None
+    if overlap:
+        l = np.arange(L)
+        apod = np.stack([l % 3 != 0, l < 24, (l >= 8) & (l < 16)]).astype(np.uint8)
+    g = synth.Geometry(n_elements=L, pitch_m=0.1 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=64, bands_hz=[(2e6, 6e6)],
+                       depths_m=(12 + 0.7 * np.arange(11)) * MM, n_x=n_x, n_sub=n_sub, apod=apod)
+    g = g.replace(**{k: v for k, v in kw.items() if k != "overlap"})
+    rng = np.random.default_rng(L + n_x)
+    rf = synth.render(g, [synth.Emitter(0.5 * MM, 15 * MM, "broadband")], rng, snr_db=20.0)
+    plan = pam.pam_plan(g, 0, "fp32")
+    try:
+        x = torch.from_numpy(np.stack([rf, rf])).cuda()
+        img = torch.full((2, plan.n_z, plan.n_x), -1.0, device="cuda")
+        nncc = torch.full_like(img, -1.0)
+        pam.pam_fd_tea_tax(plan, x, img, nncc, None, pam.alloc_workspace(plan, 2, g.n_samples))
+        torch.cuda.synchronize()
+    finally:
+        pam.pam_destroy(plan)
+    ref = T.fd_tea_tax(rf, g)
+    for f in range(2):
+        assert rel(img[f].double().cpu().numpy(), ref["I"]) <= 1e-5
+        assert np.abs(nncc[f].double().cpu().numpy() - ref["rho_n"]).max() <= 1e-4
