@@ -42,8 +42,8 @@
 //
 // The sizes without a codelet ran as dense DFT-GEMMs on the FP32 matrix cores before (4 N
 // flops per complex output against about 11 operations per point and stage): 4.14 -> 0.58 ms for
-// 4 frames of 301 x 192 pixels and 691 bins (43 TFLOP/s of the method's operations; the
-// idle stage-1 lanes, 4 of 16 here, are what it lacks to the 61 of N = 256).
+// 4 frames of 301 x 192 pixels and 691 bins (the idle stage-1 lanes, 4 of 16 here, are
+// what it lacks to the rate of N = 256).
 #pragma once
 #include <utility>
 
@@ -68,15 +68,6 @@ struct FtShape {
 template <int NN>
 __host__ __device__ constexpr int ft_depths() { return 16 * FtShape<NN>::DG / FtShape<NN>::R; }
 inline int ft_depths_of(int n) { return n > 256 ? 8 : (n > 128 ? 16 : (n > 64 ? 32 : (n > 32 ? 64 : 128))); }
-
-// LDS: staged bins [2][ff_stage_rows], stage twiddles [16 x1][16 j], (N > 256) combination
-// twiddles [2 e][16 x2][16 j], transpose blocks [4 waves][4 groups][kFtTr].
-template <int NN>
-__host__ __device__ constexpr int ft_twiddles() { return NN > 256 ? 768 : 256; }
-template <int NSUB, int NN = 256>
-inline size_t k3fft_lds() {
-  return (size_t)(2 * ff_stage_rows<NSUB, NN / 16>() + ft_twiddles<NN>() + kFtWaves * 4 * kFtTr) * sizeof(float2);
-}
 
 // The 16-byte pieces of a bin's staged inputs, 256 per pass (one per thread): one pass up to
 // N = 128 (which three sub-apertures fill exactly), two up to 256, two parts of two passes
@@ -146,7 +137,10 @@ __device__ __forceinline__ void idft4_tw(float2& x0, float2& x1, float2& x2, flo
   x1 = make_float2(fmaf(-c1, w.y, a1.x), fmaf(c1, w.x, a1.y));                   // a1 + i (y1 - y3)
   x3 = make_float2(fmaf(c1, w.y, a1.x), fmaf(-c1, w.x, a1.y));                   // a1 - i (y1 - y3)
 }
-__device__ __forceinline__ void idft16(float2 (&v)[16]) {
+// in(n2) is called when inputs n2, n2 + 4, n2 + 8 and n2 + 12 are needed, out(k1) when outputs k1, k1 + 4, k1 + 8 and
+// k1 + 12 are in v.
+template <typename In, typename Out>
+__device__ __forceinline__ void idft16(float2 (&v)[16], In&& in, Out&& out) {
   constexpr float C1 = 0.92387953251128674f;   // cos(pi / 8)
   constexpr float S1 = 0.38268343236508977f;   // sin(pi / 8) = cos(3 pi / 8)
   constexpr float R2 = 0.70710678118654752f;   // cos(pi / 4)
@@ -155,6 +149,7 @@ __device__ __forceinline__ void idft16(float2 (&v)[16]) {
   float2 T[4][4];
 #pragma unroll
   for (int n2 = 0; n2 < 4; ++n2) {
+    in(n2);
     const float2 a0 = f2add(v[n2], v[8 + n2]), a1 = f2sub(v[n2], v[8 + n2]);
     const float2 b0 = f2add(v[4 + n2], v[12 + n2]), b1 = f2sub(v[4 + n2], v[12 + n2]);
     T[n2][0] = f2add(a0, b0);
@@ -171,12 +166,14 @@ __device__ __forceinline__ void idft16(float2 (&v)[16]) {
     v[4] = f2iadd(a1, b1);
     v[12] = f2isub(a1, b1);
   }
+  out(0);
   // k1 = 1: W^1 (pi / 8), W^2 (pi / 4), W^3 (3 pi / 8)
   idft4_tw(T[0][1], T[1][1], T[2][1], T[3][1], C1, T1, R2, 1.0f, T3, S1 / C1);
   v[1] = T[0][1];
   v[5] = T[1][1];
   v[9] = T[2][1];
   v[13] = T[3][1];
+  out(1);
   // k1 = 2: W^2 (pi / 4), W^4 = i, W^6 (3 pi / 4); y1 +- y3 = R2 (u1 -+ u3)
   {
     const float2 x0 = T[0][2], x2 = T[2][2];
@@ -190,53 +187,175 @@ __device__ __forceinline__ void idft16(float2 (&v)[16]) {
     v[6] = make_float2(fmaf(-R2, d.y, a1.x), fmaf(R2, d.x, a1.y));
     v[14] = make_float2(fmaf(R2, d.y, a1.x), fmaf(-R2, d.x, a1.y));
   }
+  out(2);
   // k1 = 3: W^3 (3 pi / 8), W^6 (3 pi / 4), W^9 (9 pi / 8)
   idft4_tw(T[0][3], T[1][3], T[2][3], T[3][3], S1, T3, -R2, -1.0f, T1, -C1 / S1);
   v[3] = T[0][3];
   v[7] = T[1][3];
   v[11] = T[2][3];
   v[15] = T[3][3];
+  out(3);
 }
 
 // Two workgroups per CU (at most 256 VGPRs a lane).  At N = 512 with three sub-apertures
 // this spills a few values per bin to scratch, which measures faster (about 1.4x) than one
 // workgroup per CU without spills.
-// In-register inverse 8-point DFT of v[o..o+7], natural order in and out:
-//   v[o + k] <- sum_n v[o + n] e^{+2 pi i n k / 8}.
-// n = 4 n1 + n2, k = k1 + 2 k2: 2-point transforms over n1, twiddles e^{2 pi i n2 k1 / 8},
-// 4-point transforms over n2.
-__device__ __forceinline__ void idft8(float2 (&v)[16], int o) {
-  constexpr float R2 = 0.70710678118654752f;   // cos(pi / 4)
-  float2 T[4][2];
+// An LDS address the compiler cannot see through: accesses at constant offsets from it keep this base, so that pairs of
+// 8-byte accesses merge into one instruction (their offsets are 8 bits wide; from a shared base they do not fit).
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f2v lds_f2;
+typedef __attribute__((address_space(3))) v4f lds_f4;
+__device__ __forceinline__ float2 get2(const lds_f2* p) {
+  const f2v v = *p;
+  return make_float2(v.x, v.y);
+}
+__device__ __forceinline__ void put2(lds_f2* p, float2 v) { *p = f2v{v.x, v.y}; }
+__device__ __forceinline__ lds_f2* lds_base(float2* p) {
+  unsigned a = (unsigned)(uintptr_t)(lds_f2*)p;
+  asm volatile("" : "+v"(a));
+  return (lds_f2*)(uintptr_t)a;
+}
+
+// Stage 3 with the twiddles folded into the transform (16 and 8 points).  The twiddle of input n is
+// w_n = c_n (1 + i t_n), c_n and t_n the cosine and tangent of 2 pi n x1 / 16 K, x1 the lane's row.  u_n = y_n + i t_n y_n
+// costs two FMAs; the cosines enter the butterflies' FMAs as ratios, so a butterfly of scaled inputs takes as many
+// operations as one of plain inputs: with s_n2 = c_n2 the scale of column n2 of the first stage,
+//   a = u_n2 +- (c_{8+n2} / c_n2) u_{8+n2}, b = u_{4+n2} +- (c_{12+n2} / c_{4+n2}) u_{12+n2},
+//   T = a +- (c_{4+n2} / c_n2) (i) b,
+// and s_n2 multiplies the second stage's constant twiddles.  144 + 30 operations at 16 points instead of 144 + 64.
+// The constants depend on the lane's row only: float4s k at c[16 k] (ft_constants on the host).  A cosine of zero (n x1 a
+// quarter turn of 16 K: (8, 8) at K = 16, (4, 8) at K = 8) is stored as 2^-30, its tangent as 2^30: the product is exact.
+__device__ __forceinline__ void bfly_scaled(float2& x0, float2& x1, float2& x2, float2& x3, float al, float be, float ga) {
+  const float2 a0 = make_float2(fmaf(al, x2.x, x0.x), fmaf(al, x2.y, x0.y));
+  const float2 a1 = make_float2(fmaf(-al, x2.x, x0.x), fmaf(-al, x2.y, x0.y));
+  const float2 b0 = make_float2(fmaf(ga, x3.x, x1.x), fmaf(ga, x3.y, x1.y));
+  const float2 b1 = make_float2(fmaf(-ga, x3.x, x1.x), fmaf(-ga, x3.y, x1.y));
+  x0 = make_float2(fmaf(be, b0.x, a0.x), fmaf(be, b0.y, a0.y));
+  x2 = make_float2(fmaf(-be, b0.x, a0.x), fmaf(-be, b0.y, a0.y));
+  x1 = make_float2(fmaf(-be, b1.y, a1.x), fmaf(be, b1.x, a1.y));       // a1 + i be b1
+  x3 = make_float2(fmaf(be, b1.y, a1.x), fmaf(-be, b1.x, a1.y));
+}
+// the column of twiddles i c2 and (1 +- i) in the second stage: y0 + i c2 x2, y1 +- y3 = cr ((1 + i) x1 -+ rho (1 - i) x3)
+__device__ __forceinline__ void idft4_quarter(float2& x0, float2& x1, float2& x2, float2& x3, float c2, float cr, float rho) {
+  const float2 a0 = make_float2(fmaf(-c2, x2.y, x0.x), fmaf(c2, x2.x, x0.y));
+  const float2 a1 = make_float2(fmaf(c2, x2.y, x0.x), fmaf(-c2, x2.x, x0.y));
+  const float2 u1 = make_float2(x1.x - x1.y, x1.y + x1.x);             // (1 + i) x1
+  const float2 u3 = make_float2(x3.x + x3.y, x3.y - x3.x);             // (1 - i) x3
+  const float2 v = make_float2(fmaf(-rho, u3.x, u1.x), fmaf(-rho, u3.y, u1.y));
+  const float2 w = make_float2(fmaf(rho, u3.x, u1.x), fmaf(rho, u3.y, u1.y));
+  x0 = make_float2(fmaf(cr, v.x, a0.x), fmaf(cr, v.y, a0.y));
+  x2 = make_float2(fmaf(-cr, v.x, a0.x), fmaf(-cr, v.y, a0.y));
+  x1 = make_float2(fmaf(-cr, w.y, a1.x), fmaf(cr, w.x, a1.y));
+  x3 = make_float2(fmaf(cr, w.y, a1.x), fmaf(-cr, w.x, a1.y));
+}
+template <int NSUB>
+__device__ __forceinline__ void idft16_tw(float2 (&p)[NSUB][16], const lds_f4* c) {
+  constexpr float T1 = 0.41421356237309505f;   // tan(pi / 8)
+  constexpr float T3 = 2.41421356237309505f;   // tan(3 pi / 8)
+  // c[2 n2]: tangents of n2, 4 + n2, 8 + n2, 12 + n2; c[2 n2 + 1]: the column's three ratios and one of s1 s2 rho C1 s1;
+  // c[8], c[9]: R2 s2, (S1 / C1) rho, R2 s1, S1 s1 | (-C1 / S1) rho.  Every sub-aperture's column takes the constants
+  // while they are in registers; the next column's load during its butterflies.
+  float q[4];
+  v4f t = c[0], r = c[16];
 #pragma unroll
   for (int n2 = 0; n2 < 4; ++n2) {
-    T[n2][0] = f2add(v[o + n2], v[o + 4 + n2]);
-    T[n2][1] = f2sub(v[o + n2], v[o + 4 + n2]);
-  }
-  T[1][1] = make_float2(R2 * (T[1][1].x - T[1][1].y), R2 * (T[1][1].x + T[1][1].y));     // W8^1
-  T[2][1] = make_float2(-T[2][1].y, T[2][1].x);                                          // W8^2 = i
-  T[3][1] = make_float2(-R2 * (T[3][1].x + T[3][1].y), R2 * (T[3][1].x - T[3][1].y));    // W8^3
+    const v4f tn = c[32 * (n2 + 1)], rn = c[32 * (n2 + 1) + 16];
+    q[n2] = r[3];
 #pragma unroll
-  for (int k1 = 0; k1 < 2; ++k1) {
-    const float2 a0 = f2add(T[0][k1], T[2][k1]), a1 = f2sub(T[0][k1], T[2][k1]);
-    const float2 b0 = f2add(T[1][k1], T[3][k1]), b1 = f2sub(T[1][k1], T[3][k1]);
-    v[o + k1] = f2add(a0, b0);
-    v[o + k1 + 4] = f2sub(a0, b0);
-    v[o + k1 + 2] = f2iadd(a1, b1);
-    v[o + k1 + 6] = f2isub(a1, b1);
+    for (int i = 0; i < NSUB; ++i) {
+      float2(&v)[16] = p[i];
+      if (n2 > 0) v[n2] = tan_rot(v[n2], t[0]);
+      v[4 + n2] = tan_rot(v[4 + n2], t[1]);
+      v[8 + n2] = tan_rot(v[8 + n2], t[2]);
+      v[12 + n2] = tan_rot(v[12 + n2], t[3]);
+      // x_k1 at v[4 k1 + n2]: the order idft4 of (n2, 4 + n2, 8 + n2, 12 + n2) gives
+      bfly_scaled(v[n2], v[4 + n2], v[8 + n2], v[12 + n2], r[0], r[1], r[2]);
+    }
+    t = tn;
+    r = rn;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int i = 0; i < NSUB; ++i) {
+    float2(&v)[16] = p[i];
+    // second stage over n2 for each k1, in place in v[4 k1 ..]
+    bfly_scaled(v[0], v[1], v[2], v[3], q[1], q[0], q[2]);
+    idft4_tw(v[4], v[5], v[6], v[7], q[3], T1, t[0], 1.0f, T3, t[1]);
+    idft4_quarter(v[8], v[9], v[10], v[11], q[1], t[2], q[2]);
+    idft4_tw(v[12], v[13], v[14], v[15], t[3], T3, -t[0], -1.0f, T1, r[0]);
+    // v[4 k1 + k2] holds output k1 + 4 k2
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1)
+#pragma unroll
+      for (int k2 = k1 + 1; k2 < 4; ++k2) {
+        const float2 x = v[4 * k1 + k2];
+        v[4 * k1 + k2] = v[4 * k2 + k1];
+        v[4 * k2 + k1] = x;
+      }
+  }
+}
+// 8 points at v[O ..]: first stage of two inputs n2, 4 + n2; second stage k1 = 0 and k1 = 1 (twiddles W8^n2)
+template <int O>
+__device__ __forceinline__ void idft8_tw(float2 (&v)[16], const v4f (&c)[4]) {
+  // c: t1 t2 t3 t4 | t5 t6 t7 al0 | al1 al2 al3 s1 | s2 rho R2 s1 -
+  const float al[4] = {c[1][3], c[2][0], c[2][1], c[2][2]};
+  const float t[8] = {0.f, c[0][0], c[0][1], c[0][2], c[0][3], c[1][0], c[1][1], c[1][2]};
+  float2 a[4], b[4];
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+    const float2 x = n2 > 0 ? tan_rot(v[O + n2], t[n2]) : v[O], y = tan_rot(v[O + 4 + n2], t[4 + n2]);
+    a[n2] = make_float2(fmaf(al[n2], y.x, x.x), fmaf(al[n2], y.y, x.y));
+    b[n2] = make_float2(fmaf(-al[n2], y.x, x.x), fmaf(-al[n2], y.y, x.y));
+  }
+  bfly_scaled(a[0], a[1], a[2], a[3], c[3][0], c[2][3], c[3][1]);
+  idft4_quarter(b[0], b[1], b[2], b[3], c[3][0], c[3][2], c[3][1]);
+#pragma unroll
+  for (int k2 = 0; k2 < 4; ++k2) {
+    v[O + 2 * k2] = a[k2];
+    v[O + 2 * k2 + 1] = b[k2];
   }
 }
 
-// The K-point transforms of stage 3, depth D's at p[D CW ..].
-template <int K, int O>
-__device__ __forceinline__ void idft_at(float2 (&p)[16]) {
-  if constexpr (K == 16) idft16(p);
-  else if constexpr (K == 8) idft8(p, O);
-  else dft_small<1, K, O>(p);
+// y w with the roundings written out (the compiler is free to contract a plain product either way)
+__device__ __forceinline__ float2 twiddled(float2 y, float2 w) {
+  return make_float2(fmaf(y.x, w.x, -(y.y * w.y)), fmaf(y.y, w.x, y.x * w.y));
 }
-template <int NN, int... D>
-__device__ __forceinline__ void stage3(float2 (&p)[16], std::integer_sequence<int, D...>) {
-  (idft_at<FtShape<NN>::K, D * FtShape<NN>::CW>(p), ...);
+
+// Whether stage 3 of N columns takes its twiddles itself (else they multiply the stage-1 outputs), and the size of the
+// table in LDS: [10 or 4 float4][16 rows], or [16 x1][16 j] factors.  The pair sums (COH) keep the plain twiddles: they
+// become BF16 features, where a last-bit difference moves the network's output by a BF16 rounding.
+template <int NN, bool COH = false>
+__host__ __device__ constexpr bool ft_folded() { return !COH && (FtShape<NN>::K == 16 || FtShape<NN>::K == 8); }
+template <int NN, bool COH = false>
+__host__ __device__ constexpr int ft_stage_tw() { return !ft_folded<NN, COH>() ? 256 : (FtShape<NN>::K == 16 ? 320 : 128); }
+
+// LDS: staged bins [2][ff_stage_rows], the stage-3 constants or stage twiddles, (N > 256) combination
+// twiddles [2 e][16 x2][16 j], transpose blocks [4 waves][4 groups][kFtTr].
+template <int NN, bool COH = false>
+__host__ __device__ constexpr int ft_twiddles() { return ft_stage_tw<NN, COH>() + (NN > 256 ? 512 : 0); }
+template <int NSUB, int NN = 256, bool COH = false>
+inline size_t k3fft_lds() {
+  return (size_t)(2 * ff_stage_rows<NSUB, NN / 16>() + ft_twiddles<NN, COH>() + kFtWaves * 4 * kFtTr) * sizeof(float2);
+}
+
+// The K-point transforms of stage 3 for every sub-aperture, depth D's at p[i][D CW ..]; c: the lane's constants (folded
+// forms).
+template <int NN, bool FOLDED, int NSUB, int... D>
+__device__ __forceinline__ void stage3(float2 (&p)[NSUB][16], const lds_f4* c, std::integer_sequence<int, D...>) {
+  constexpr int K = FtShape<NN>::K;
+  if constexpr (K == 16 && FOLDED) {
+    idft16_tw(p, c);
+  } else if constexpr (K == 16) {
+#pragma unroll
+    for (int i = 0; i < NSUB; ++i) idft16(p[i], [](int) {}, [](int) {});
+  } else if constexpr (K == 8) {
+    const v4f cc[4] = {c[0], c[16], c[32], c[48]};
+#pragma unroll
+    for (int i = 0; i < NSUB; ++i) (idft8_tw<8 * D>(p[i], cc), ...);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NSUB; ++i) (dft_small<1, K, D * FtShape<NN>::CW>(p[i]), ...);
+  }
 }
 
 // kz(q) = kz(N - q), so the propagator of a column's m = 9 .. 15 is that of another column's 15 - m at the same
@@ -271,21 +390,40 @@ __device__ __forceinline__ float partner_column(float v) {
   }
 }
 
-template <int NSUB, bool COH = false, int NN = 256>
+// Bound: the vector ALUs' issue (about 1,470 instructions per wave and bin at N = 256 and three sub-apertures), as long
+// as the LDS instructions keep out of each other's way.  A wave issues 82 of those a bin, and in bursts (sixteen row
+// writes, eight row reads, eight coefficient reads in a row) they stall both waves of a SIMD in the LDS queue, so they
+// are spread over the arithmetic, held in place by scheduling barriers: coefficients in two halves, the previous
+// sub-aperture's row reads between the columns of stage 1, row writes after each column of its second stage, and the
+// stage-3 constants read once a bin for all sub-apertures.  64 frames of the benchmark array (512 x 256, 768 bins): 17.1
+// ms with twiddles multiplied between the stages, 17.5 with them folded but the LDS instructions in bursts, 15.7 so.
+// One frame of 1,024 x 512 pixels and 3,072 bins: 6.37 -> 5.55 ms; 4 of 301 x 192 and 691: 0.578 -> 0.535.
+// The mirrored propagator values through LDS instead of two DPP moves and a select (42 vector instructions fewer)
+// measured the same at N = 256 and 6 % slower at 512.
+//
+// EARLY: with one sub-aperture (up to 256 columns) the next bin's inputs are stored and the bin's barrier passed before
+// stage 3, which ends their registers there; with three it measured 1 % slower at 512 columns.
+// LEAN (with the pair sums): EARLY and the twiddles read where they are used, 164 registers instead of 194, so that three
+// workgroups fit a CU.  64 frames of the benchmark array 8.67 -> 7.76 ms, 24 frames in two bin splits 3.35 -> 3.05; but
+// 16 frames, two workgroups per CU, 2.27 -> 2.45, so launches of at most two per CU keep the other form (2.28).
+template <int NSUB, bool COH = false, int NN = 256, bool LEAN = false>
 __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
   static_assert(!COH || (NSUB == 1 && NN == 256), "pair cross-spectra come with the full-aperture sums at N = 256");
   constexpr int NP = AccCount<NSUB>::pairs;
   constexpr int N = NN;
   constexpr int R = FtShape<NN>::R, K = FtShape<NN>::K, DG = FtShape<NN>::DG, CW = FtShape<NN>::CW;
   constexpr int PX = DG * K;                                       // pixels per lane
+  constexpr bool FOLDED = ft_folded<NN, COH>();
+  constexpr bool EARLY = NSUB == 1 && R == 1 && (!COH || LEAN);
+  constexpr bool SPREAD = !COH || LEAN;
   constexpr int ROWS = NN / 16;
   extern __shared__ float2 lds_ft[];
   float2* stage = lds_ft;                                          // [2][ff_stage_rows]
-  float2* twl = lds_ft + 2 * ff_stage_rows<NSUB, ROWS>();          // [16 x1][16 j] (+ [2 e][16 x2][16 j])
+  float2* twl = lds_ft + 2 * ff_stage_rows<NSUB, ROWS>();          // stage-3 constants or twiddles (+ [2 e][16 x2][16 j])
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int g = lane >> 4, j = lane & 15;
   const int e = R == 2 ? (g & 1) : 0;                              // parity of q (N > 256)
-  float2* tr = twl + ft_twiddles<NN>() + (w * 4 + g) * kFtTr;     // this group's transpose block
+  float2* tr = twl + ft_twiddles<NN, COH>() + (w * 4 + g) * kFtTr;     // this group's transpose block
   // stage-1 column of this lane (idle lanes repeat the last one) and its staged row
   const int col = K == CW ? j % CW : min(j % CW, K - 1);
   const int srow = R == 1 ? col : 2 * col + e;
@@ -297,11 +435,14 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
   const int depth1 = depth + j / CW;
   const double z = depth1 < a.n_z ? a.z[depth1] : 0.0;
 
-  // stage-1 -> stage-3 twiddles e^{2 pi i q2 x1 / 16 K} and (N > 256) the combination twiddles
+  // stage-3 constants or twiddles e^{2 pi i q2 x1 / 16 K}, and (N > 256) the combination twiddles
   // e^{2 pi i (j + 16 x2 + e N/2) / N}, the e = 1 half the negated e = 0 half (FP32 tables built in FP64)
-  for (int k = tid; k < ft_twiddles<NN>(); k += 256) {
-    const float2 t = k < 256 ? a.ff_tw_vec[k] : a.ff_tw2_vec[(k - 256) & 255];
-    twl[k] = k < 512 ? t : make_float2(-t.x, -t.y);
+  constexpr int TW = ft_stage_tw<NN, COH>();
+  for (int k = tid; k < TW; k += 256) twl[k] = a.ff_tw_vec[k];
+  if constexpr (R == 2) {
+    const float2 t = a.ff_tw2_vec[tid];
+    twl[TW + tid] = t;
+    twl[TW + 256 + tid] = make_float2(-t.x, -t.y);
   }
 
   float accS[NSUB][PX];
@@ -316,6 +457,13 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
 #pragma unroll
     for (int q = 0; q < (COH ? 4 : 1); ++q) accG[q][x2] = 0.f;
   }
+
+  lds_f2* const tcol = lds_base(tr + j);                            // column j of the transpose block
+  lds_f2* const trow = lds_base(tr + j * kFfRow);                   // row j
+  lds_f2* const grow = lds_base(stage + srow * kFfRow);             // staged coefficients of the lane's row
+  lds_f2* const twj = lds_base(twl + (FOLDED ? 2 : 1) * j);   // this row's constants or this column's twiddles
+  const lds_f4* const twc4 = (const lds_f4*)twj;
+  lds_f2* const twc = R == 2 ? lds_base(twl + TW + 256 * e + j) : twj;
 
   FtPiece<NSUB, NN> pc(tid);
   if (wg.b_begin < wg.b_end) {
@@ -356,68 +504,121 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
         H[m] = self ? H[16 - m] : o;
       }
     }
+    // Stage 1 and the transpose sub-aperture by sub-aperture (one's row reads are in flight during the next one's stage
+    // 1), then stage 3 of all of them, so that each constant is read once a bin.
     float2 p[NSUB][16];
+    // S_i and C_ij sums over the bins (Eq. 4): sum |p_i|^2, sum Re(p_i conj p_j)
+    auto add_s = [&](int i) {
+#pragma unroll
+      for (int px = 0; px < PX; ++px) {
+        const float2 v = p[i][px / K * CW + px % K];               // of depth px / K
+        accS[i][px] = fmaf(v.x, v.x, fmaf(v.y, v.y, accS[i][px]));
+      }
+    };
+    auto add_c = [&](int c, int i, int j2) {
+#pragma unroll
+      for (int px = 0; px < PX; ++px) {
+        const float2 v = p[i][px / K * CW + px % K], u = p[j2][px / K * CW + px % K];
+        accC[c][px] = fmaf(v.x, u.x, fmaf(v.y, u.y, accC[c][px]));
+      }
+    };
+    // half h of row x1 = j of the transpose block
+    auto rows = [&](float2 (&v)[16], int h) {
+#pragma unroll
+      for (int k = 4 * h; k < 4 * h + 4; ++k) {
+        const v4f yy = *(lds_f4*)(trow + 2 * k);
+        v[2 * k] = make_float2(yy.x, yy.y);
+        v[2 * k + 1] = make_float2(yy.z, yy.w);
+      }
+    };
+    constexpr bool TWREG = !FOLDED && !LEAN;                       // a column's twiddles in registers for the bin
+    float2 tw[TWREG ? 16 : 1];
+    if constexpr (TWREG) {
+#pragma unroll
+      for (int x1 = 1; x1 < 16; ++x1) tw[x1] = get2(twj + x1 * 16);
+    }
+    v4f ga[4], gb[4];
+    auto coeffs = [&](int i, int h, v4f (&g)[4]) {                 // staged pairs 2 k + h: inputs 4 k + 2 h, 4 k + 2 h + 1
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        g[k] = *(lds_f4*)(grow + ((b - wg.b_begin) & 1) * ff_stage_rows<NSUB, ROWS>() + i * ROWS * kFfRow + 4 * k + 2 * h);
+    };
 #pragma unroll
     for (int i = 0; i < NSUB; ++i) {
-      const float4* gr = reinterpret_cast<const float4*>(st + (i * ROWS + srow) * kFfRow);
+      coeffs(i, 0, ga);
+      idft16(p[i], [&](int n2) {
+        if (n2 & 1) return;
+        if (n2 == 0) coeffs(i, 1, gb);
+        if constexpr (SPREAD) __builtin_amdgcn_sched_barrier(0);
+        if (n2 == 2 && i > 0) rows(p[i - 1], 0);
+        v4f (&g)[4] = n2 ? gb : ga;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float4 gg = gr[k];
-        p[i][2 * k] = cmul(H[2 * k], make_float2(gg.x, gg.y));
-        p[i][2 * k + 1] = cmul(H[2 * k + 1], make_float2(gg.z, gg.w));
+        for (int k = 0; k < 4; ++k) {
+          const int m = 4 * k + n2;
+          p[i][m] = cmul(H[m], make_float2(g[k].x, g[k].y));
+          p[i][m + 1] = cmul(H[m + 1], make_float2(g[k].z, g[k].w));
+        }
+      }, [&](int k1) {                                             // Y(x1, q2 = j), x1 = 0..15
+        if (k1 == 0) {
+          if (i > 0) rows(p[i - 1], 1);
+          __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int x1 = k1; x1 < 16; x1 += 4) {
+          if constexpr (FOLDED) put2(tcol + x1 * kFfRow, p[i][x1]);
+          else if constexpr (LEAN) put2(tcol + x1 * kFfRow, twiddled(p[i][x1], get2(twj + x1 * 16)));
+          else put2(tcol + x1 * kFfRow, x1 == 0 ? p[i][x1] : twiddled(p[i][x1], tw[x1]));
+        }
+        if constexpr (SPREAD) __builtin_amdgcn_sched_barrier(0);
+      });
+      __builtin_amdgcn_wave_barrier();
+      if (R == 2 && i == 0 && more) {
+        pc.store(nxt, 0);
+        pc.load(a, f, b + 1, tid, 1);
       }
     }
+    if constexpr (EARLY) {
+      if (more) pc.store(nxt, R - 1);
+      __syncthreads();
+    }
+    rows(p[NSUB - 1], 0);
+    rows(p[NSUB - 1], 1);
+    stage3<NN, FOLDED>(p, twc4, std::make_integer_sequence<int, DG>());    // depth d: p(j + 16 x2) in p[i][d CW + x2]
+    // the fields are final here (sunk to the fold, the last butterflies or the combination would keep their inputs live)
+    if constexpr (R == 2) {
+      // p(x' + e N/2) = P_0(x') + w P_1(x'), x' = j + 16 x2, w = e^{2 pi i (x' + e N/2) / N}: the even row of
+      // each row pair (e = 0) holds P_0(x'), the odd row P_1(x'), and one row swap hands both to both rows
 #pragma unroll
-    for (int i = 0; i < NSUB; ++i) {
-      idft16(p[i]);                                                // Y(x1, q2 = j), x1 = 0..15
+      for (int x2 = 0; x2 < K; ++x2) {
+        const float2 w2 = get2(twc + x2 * 16);
 #pragma unroll
-      for (int x1 = 0; x1 < 16; ++x1)   // (the twiddle of x1 = 0 is exactly 1; skipped beyond N = 256 only,
-                                        // where it shortens the spill, at N = 512 76 -> 20 bytes a lane; at
-                                        // N = 128 and 256 the compiler's allocation then spills)
-        tr[x1 * kFfRow + j] = (R == 2 && x1 == 0) ? p[i][0] : cmul(p[i][x1], twl[x1 * 16 + j]);
-      __builtin_amdgcn_wave_barrier();
-      const float4* yr = reinterpret_cast<const float4*>(tr + j * kFfRow);   // row x1 = j
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float4 yy = yr[k];
-        p[i][2 * k] = make_float2(yy.x, yy.y);
-        p[i][2 * k + 1] = make_float2(yy.z, yy.w);
-      }
-      __builtin_amdgcn_wave_barrier();
-      stage3<NN>(p[i], std::make_integer_sequence<int, DG>());     // depth d: p(j + 16 x2) in p[i][d CW + x2]
-      if constexpr (R == 2) {
-        // p(x' + e N/2) = P_0(x') + w P_1(x'), x' = j + 16 x2, w = e^{2 pi i (x' + e N/2) / N}: the even row of
-        // each row pair (e = 0) holds P_0(x'), the odd row P_1(x'), and one row swap hands both to both rows
-#pragma unroll
-        for (int x2 = 0; x2 < K; ++x2) {
+        for (int i = 0; i < NSUB; ++i) {
           const float2 re = rows_even_odd(p[i][x2].x), im = rows_even_odd(p[i][x2].y);   // (P_0, P_1) parts
-          const float2 w2 = twl[256 + 256 * e + x2 * 16 + j];
           p[i][x2] = make_float2(fmaf(w2.x, re.y, fmaf(-w2.y, im.y, re.x)), fmaf(w2.x, im.y, fmaf(w2.y, re.y, im.x)));
-          // combined here: sunk to the fold, the two swapped halves would stay live instead of the result
           asm volatile("" : "+v"(p[i][x2].x), "+v"(p[i][x2].y));
         }
-        // the next bin's second half once every transform is done (fewer values live through the transforms)
-        if (i == NSUB - 1 && more) {
-          pc.store(nxt, 0);
-          pc.load(a, f, b + 1, tid, 1);
-        }
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NSUB; ++i)
+#pragma unroll
+        for (int d = 0; d < DG; ++d)
+#pragma unroll
+          for (int k = 0; k < K; ++k) asm volatile("" : "+v"(p[i][d * CW + k].x), "+v"(p[i][d * CW + k].y));
     }
-    // fold: S_i = sum |p_i|^2, C_ij = sum Re(p_i conj p_j) (Eq. 4) over the bins
 #pragma unroll
-    for (int px = 0; px < PX; ++px) {
-      const int x2 = px / K * CW + px % K;                         // of depth px / K
+    for (int i = 0; i < NSUB; ++i) add_s(i);
+    if constexpr (NSUB == 3) {
+      add_c(0, 0, 1);
+      add_c(1, 1, 2);
+      add_c(2, 2, 0);
+    } else if constexpr (NSUB == 2) {
+      add_c(0, 0, 1);
+    }
+    if constexpr (COH) {
 #pragma unroll
-      for (int i = 0; i < NSUB; ++i) accS[i][px] = fmaf(p[i][x2].x, p[i][x2].x, fmaf(p[i][x2].y, p[i][x2].y, accS[i][px]));
-      if constexpr (NSUB == 3) {
-        accC[0][px] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][px]));
-        accC[1][px] = fmaf(p[1][x2].x, p[2][x2].x, fmaf(p[1][x2].y, p[2][x2].y, accC[1][px]));
-        accC[2][px] = fmaf(p[2][x2].x, p[0][x2].x, fmaf(p[2][x2].y, p[0][x2].y, accC[2][px]));
-      } else if constexpr (NSUB == 2) {
-        accC[0][px] = fmaf(p[0][x2].x, p[1][x2].x, fmaf(p[0][x2].y, p[1][x2].y, accC[0][px]));
-      }
-      if constexpr (COH) {
-        const float pr = p[0][x2].x, pi = p[0][x2].y;
+      for (int px = 0; px < PX; ++px) {
+        const float pr = p[0][px].x, pi = p[0][px].y;
         const float lr = lane_xor1(pr), li = lane_xor1(pi);
         const float zr = lane_xor16(pr), zi = lane_xor16(pi);
         accG[0][px] = fmaf(pr, lr, fmaf(pi, li, accG[0][px]));
@@ -426,8 +627,10 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
         accG[3][px] = fmaf(pi, zr, fmaf(-pr, zi, accG[3][px]));
       }
     }
-    if (more) pc.store(nxt, R - 1);
-    __syncthreads();
+    if constexpr (!EARLY) {
+      if (more) pc.store(nxt, R - 1);
+      __syncthreads();
+    }
   }
   constexpr int NA = COH ? 5 : AccCount<NSUB>::total;
   const size_t plane = (size_t)a.n_z * N;

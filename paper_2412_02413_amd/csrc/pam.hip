@@ -155,6 +155,59 @@ pam_status_t upload(pam_plan_s* p, T** dst, const T* src, size_t n) {
   return PAM_OK;
 }
 
+// The vector FFT kernel's table for N columns, K = N / 16 (N / 32 beyond 256) points in stage 3.  K = 16 and 8: per row
+// x1 the constants idft16_tw / idft8_tw fold the twiddles with, float4 k of row x1 at [k][x1].  Other K, and plain: the twiddles
+// e^{2 pi i q2 x1 / 16 K} at [x1][j], q2 = j % CW the stage-1 column of lane j (K of the CW lanes of a depth hold one, the
+// others a zero).
+std::vector<float2> ft_table(int N, bool plain) {
+  const int K = N > 256 ? N / 32 : N / 16, CW = K <= 2 ? 2 : (K <= 4 ? 4 : (K <= 8 ? 8 : 16));
+  if (plain || (K != 16 && K != 8)) {
+    std::vector<float2> tw(256, make_float2(0.f, 0.f));
+    for (int x1 = 0; x1 < 16; ++x1)
+      for (int j = 0; j < 16; ++j) {
+        const int q2 = j % CW;
+        const double th = 2.0 * kPi * (double)(q2 * x1) / (double)(16 * K);
+        if (q2 < K) tw[x1 * 16 + j] = make_float2((float)std::cos(th), (float)std::sin(th));
+      }
+    return tw;
+  }
+  const int n4 = K == 16 ? 10 : 4;
+  std::vector<float2> tw(n4 * 32);
+  float* out = &tw[0].x;
+  for (int x1 = 0; x1 < 16; ++x1) {
+    double c[16], t[16];
+    for (int n = 0; n < K; ++n) {
+      const int turn = n * x1 % (16 * K);                       // of 16 K
+      const double th = 2.0 * kPi * (double)turn / (double)(16 * K);
+      const bool quarter = turn == 4 * K || turn == 12 * K;     // exact zero of the cosine
+      c[n] = quarter ? std::ldexp(1.0, -30) : std::cos(th);
+      t[n] = (quarter ? (turn == 4 * K ? 1.0 : -1.0) : std::sin(th)) / c[n];
+    }
+    const double C1 = std::cos(kPi / 8), S1 = std::sin(kPi / 8), R2 = std::cos(kPi / 4);
+    double v[40] = {};
+    if (K == 16) {
+      const double s1 = c[1], s2 = c[2], rho = c[3] / c[1];
+      const double q[9] = {s1, s2, rho, C1 * s1, R2 * s2, S1 / C1 * rho, R2 * s1, S1 * s1, -C1 / S1 * rho};
+      for (int n2 = 0; n2 < 4; ++n2) {
+        for (int n1 = 0; n1 < 4; ++n1) v[8 * n2 + n1] = t[4 * n1 + n2];
+        v[8 * n2 + 4] = c[8 + n2] / c[n2];
+        v[8 * n2 + 5] = c[4 + n2] / c[n2];
+        v[8 * n2 + 6] = c[12 + n2] / c[4 + n2];
+        v[8 * n2 + 7] = q[n2];
+      }
+      std::copy(q + 4, q + 9, v + 32);
+    } else {
+      for (int n = 1; n < 8; ++n) v[n - 1] = t[n];
+      for (int n2 = 0; n2 < 4; ++n2) v[7 + n2] = c[4 + n2] / c[n2];
+      const double q[4] = {c[1], c[2], c[3] / c[1], R2 * c[1]};
+      std::copy(q, q + 4, v + 11);
+    }
+    for (int k = 0; k < n4; ++k)
+      for (int e = 0; e < 4; ++e) out[(k * 16 + x1) * 4 + e] = (float)v[4 * k + e];
+  }
+  return tw;
+}
+
 pam_status_t validate(const pam_geometry_t* g) {
   if (!g) return PAM_ERR_INVALID_ARG;
   if (g->n_elements < 1 || !finite_pos(g->pitch_m) || !finite_pos(g->fs_hz) || !finite_pos(g->c_mps))
@@ -392,10 +445,11 @@ pam_status_t layout(const pam_plan_s* p, int64_t F, int n_t, pam_workspace_layou
 }
 
 // Where a K3 dispatch goes: a launch on stream st, or, with occ set, no launch but the
-// number of the kernel's workgroups one CU holds (written to *occ).
+// number of the kernel's workgroups one CU holds (written to *occ).  n_cus: compute units of the launch's device.
 struct Target {
   hipStream_t st;
   int* occ;
+  int n_cus = 0;
 };
 
 // K3 kernels: NC consumer + NC producer waves, NC*32 columns per workgroup.
@@ -443,15 +497,13 @@ hipError_t launch_prec16(int precision, const pam::K3Args& a, int blocks, Target
   }
 }
 
-// Kernels with more than 64 KB of dynamic LDS: the attribute is set before each launch
-// for the largest size the instantiation takes.
+// Kernels with more than 64 KB of dynamic LDS: the attribute is set before each launch.
 template <typename K>
-hipError_t launch_big_lds(K kernel, int nw, size_t lds, size_t lds_max, const pam::K3Args& a,
-                          const pam::K3Groups& grp, int blocks, Target st) {
+hipError_t launch_big_lds(K kernel, int nw, size_t lds, const pam::K3Args& a, const pam::K3Groups& grp, int blocks,
+                          Target st) {
   const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return attr;
-  if (lds > lds_max) return hipErrorInvalidValue;
   if (st.occ)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(st.occ, reinterpret_cast<const void*>(kernel), nw * 64, lds);
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(nw * 64), lds, st.st, a, grp);
@@ -463,10 +515,10 @@ hipError_t launch_ff_r(int precision, const pam::K3Args& a, const pam::K3Groups&
   using namespace pam;
   const size_t lds = k3ff_lds<NSUB, R>();
   switch (precision) {
-    case PAM_PREC_SPLIT_BF16: return launch_big_lds(k3ff<__bf16, 3, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
-    case PAM_PREC_SPLIT_FP16: return launch_big_lds(k3ff<_Float16, 3, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
-    case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
-    case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, NSUB, false, R>, kFfWaves, lds, lds, a, grp, blocks, st);
+    case PAM_PREC_SPLIT_BF16: return launch_big_lds(k3ff<__bf16, 3, NSUB, false, R>, kFfWaves, lds, a, grp, blocks, st);
+    case PAM_PREC_SPLIT_FP16: return launch_big_lds(k3ff<_Float16, 3, NSUB, false, R>, kFfWaves, lds, a, grp, blocks, st);
+    case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, NSUB, false, R>, kFfWaves, lds, a, grp, blocks, st);
+    case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, NSUB, false, R>, kFfWaves, lds, a, grp, blocks, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -475,8 +527,7 @@ hipError_t launch_ff_r(int precision, const pam::K3Args& a, const pam::K3Groups&
 template <int NSUB, int NN = 32>
 hipError_t launch_fft(const pam::K3Args& a, const pam::K3Groups& grp, int blocks, Target st) {
   if (a.N == NN)
-    return launch_big_lds(pam::k3fft<NSUB, false, NN>, pam::kFtWaves, pam::k3fft_lds<NSUB, NN>(),
-                          pam::k3fft_lds<NSUB, NN>(), a, grp, blocks, st);
+    return launch_big_lds(pam::k3fft<NSUB, false, NN>, pam::kFtWaves, pam::k3fft_lds<NSUB, NN>(), a, grp, blocks, st);
   if constexpr (NN < kMaxNx) return launch_fft<NSUB, NN + 32>(a, grp, blocks, st);
   return hipErrorInvalidValue;
 }
@@ -517,11 +568,15 @@ hipError_t launch_k3(int precision, int n_sub, const LaunchShape& s, const pam::
     using namespace pam;
     const size_t lds = k3ff_lds<1>();
     switch (precision) {
-      case PAM_PREC_SPLIT_BF16: return launch_big_lds(k3ff<__bf16, 3, 1, true>, kFfWaves, lds, lds, a, grp, blocks, st);
-      case PAM_PREC_SPLIT_FP16: return launch_big_lds(k3ff<_Float16, 3, 1, true>, kFfWaves, lds, lds, a, grp, blocks, st);
-      case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, 1, true>, kFfWaves, lds, lds, a, grp, blocks, st);
-      case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, 1, true>, kFfWaves, lds, lds, a, grp, blocks, st);
-      default: return launch_big_lds(k3fft<1, true>, kFtWaves, k3fft_lds<1>(), k3fft_lds<1>(), a, grp, blocks, st);
+      case PAM_PREC_SPLIT_BF16: return launch_big_lds(k3ff<__bf16, 3, 1, true>, kFfWaves, lds, a, grp, blocks, st);
+      case PAM_PREC_SPLIT_FP16: return launch_big_lds(k3ff<_Float16, 3, 1, true>, kFfWaves, lds, a, grp, blocks, st);
+      case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, 1, true>, kFfWaves, lds, a, grp, blocks, st);
+      case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, 1, true>, kFfWaves, lds, a, grp, blocks, st);
+      default:
+        // more workgroups than two per CU: the form of which three fit (both measured at k3fft)
+        if (blocks > 2 * st.n_cus)
+          return launch_big_lds(k3fft<1, true, 256, true>, kFtWaves, k3fft_lds<1, 256, true>(), a, grp, blocks, st);
+        return launch_big_lds(k3fft<1, true>, kFtWaves, k3fft_lds<1, 256, true>(), a, grp, blocks, st);
     }
   }
   switch (n_sub) {
@@ -700,18 +755,13 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
           ff_tw2[l * 8 + v] = make_float2((float)std::cos(th), (float)std::sin(th));
         }
   } else if (p->ff) {
-    // vector FFT kernel: [x1][j] = e^{2 pi i q2 x1 / 16 K}, q2 = j % CW the stage-1 column of lane j (K of the CW
-    // lanes of a depth hold one, the others a zero) and, beyond N = 256, [x2][j] = e^{2 pi i (j + 16 x2) / N}
-    const int K = N > 256 ? N / 32 : N / 16, CW = K <= 2 ? 2 : (K <= 4 ? 4 : (K <= 8 ? 8 : 16));
-    ff_tw_vec.assign(256, make_float2(0.f, 0.f));
+    // vector FFT kernel: stage-3 constants or twiddles and, beyond N = 256, [x2][j] = e^{2 pi i (j + 16 x2) / N}
+    ff_tw_vec = ft_table(N, p->coherence != 0);
     ff_tw2_vec.assign(256, make_float2(0.f, 0.f));
-    for (int x1 = 0; x1 < 16; ++x1)
+    for (int x2 = 0; x2 < 16; ++x2)
       for (int j = 0; j < 16; ++j) {
-        const int q2 = j % CW;
-        const double th = 2.0 * kPi * (double)(q2 * x1) / (double)(16 * K);
-        if (q2 < K) ff_tw_vec[x1 * 16 + j] = make_float2((float)std::cos(th), (float)std::sin(th));
-        const double th2 = 2.0 * kPi * (double)(j + 16 * x1) / (double)N;
-        if (N > 256) ff_tw2_vec[x1 * 16 + j] = make_float2((float)std::cos(th2), (float)std::sin(th2));
+        const double th = 2.0 * kPi * (double)(j + 16 * x2) / (double)N;
+        if (N > 256) ff_tw2_vec[x2 * 16 + j] = make_float2((float)std::cos(th), (float)std::sin(th));
       }
   }
 
@@ -794,7 +844,8 @@ pam_status_t pam_plan(const pam_geometry_t* g, int device, pam_plan_t* out) {
       free_plan(p);
       return PAM_ERR_DEVICE;
     }
-    p->k3_slots = occ * cus;
+    // (with coherence two per CU whatever fits: the split orders the FP32 sums, and these become BF16 features)
+    p->k3_slots = (p->coherence && p->precision == PAM_PREC_FP32 ? std::min(occ, 2) : occ) * cus;
     p->n_cus = cus;
   }
   *out = p;
@@ -1085,7 +1136,7 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
     const pam::K3Groups none{};
     const long long blocks = (long long)q.F * q.s.n_dt * q.s.n_xg * q.s.n_split;
     if (blocks > 0x7fffffffLL) return PAM_ERR_UNSUPPORTED;
-    if (launch_k3(p->precision, p->n_sub, q.s, args_for(q), none, (int)blocks, Target{stream, nullptr}, p->coherence) !=
+    if (launch_k3(p->precision, p->n_sub, q.s, args_for(q), none, (int)blocks, Target{stream, nullptr, p->n_cus}, p->coherence) !=
         hipSuccess)
       return PAM_ERR_DEVICE;
     return PAM_OK;
@@ -1155,7 +1206,7 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
       blocks += (long long)q.F * q.s.n_dt * q.s.n_xg * q.s.n_split;
     }
     if (blocks > 0x7fffffffLL) return PAM_ERR_UNSUPPORTED;
-    if (launch_k3(p->precision, p->n_sub, first->s, args_for(*first), grp, (int)blocks, Target{stream, nullptr}, p->coherence) !=
+    if (launch_k3(p->precision, p->n_sub, first->s, args_for(*first), grp, (int)blocks, Target{stream, nullptr, p->n_cus}, p->coherence) !=
         hipSuccess)
       return PAM_ERR_DEVICE;
   } else {
