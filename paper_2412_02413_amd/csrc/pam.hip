@@ -332,8 +332,12 @@ int64_t k3_spare_planes(const pam_plan_s* p, bool full = true) {
 // start and its partial-sum write, and every split beyond the first costs K4 one more
 // partial-sum plane per frame (n_acc pix floats, read at about 4 TB/s against about 5 us
 // per bin).  Returns the bins-per-workgroup cap b (every group splits into ceil(n_sel / b)
-// parts) that minimises the estimate, the largest such b on ties, at least 8 bins (or the
-// widest band when narrower), among the caps whose splits fit the spare planes.
+// parts) that minimises the estimate, the largest such b on ties, at least 4 bins (or the
+// widest band when narrower), among the caps whose splits fit the spare planes.  Against at
+// least 8 bins one frame of 151 x 128 pixels and 205 bins takes 45.7 us instead of 53.1, one
+// of 93 x 384 65.9 instead of 82.1; 2 bins measure the same as 4 there and worse with one or
+// two sub-apertures (27.5 against 26.6 us).  Plans with coherence keep 8: their sums become
+// BF16 features, where another order of the FP32 sums moves the network's output.
 int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr,
                bool full = true) {
   const LaunchShape t = k3_tiles(p);
@@ -351,7 +355,7 @@ int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, d
   // top of each such piece: for every group g and split count s, the largest cap that splits g s ways
   // (n_g for s = 1, ceil(n_g / (s - 1)) - 1 after), in decreasing order (a merge over the groups' sequences,
   // no storage).  This equals trying every cap.
-  const int min_b = std::min(8, max_n);
+  const int min_b = std::min(p->coherence ? 8 : 4, max_n);
   auto top = [&](int g, int s) { return s == 1 ? n_sel[g] : (n_sel[g] + s - 2) / (s - 1) - 1; };
   int next_s[pam::kMaxGroups];
   int live = 0;
@@ -918,6 +922,7 @@ pam_status_t grouped_layout(const pam_plan_s* p, const pam_group_t* groups, int 
     cap[g] = k3_bin_cap(p, &F[g], &n_sel[g], 1, &c, full);
     separate += c;
   }
+  separate += std::max(0, live - 1);   // each further launch: about one bin-time (5 us) between its start and its drain
   *one_launch = false;
   if (p->ff && live > 1) {
     double together = 0;
