@@ -205,8 +205,8 @@ class UNet:
         dz = self._buf("dz", (P0, 2), torch.float32)
         loss = self._buf("loss", (3,), torch.float32)   # BCE mask, BCE error head, weighted mask L1
         loss.zero_()
-        for g in self.grads.values():
-            g.zero_()
+        # one multi-tensor launch instead of a fill per parameter (30 of 2.9 us each for four levels)
+        torch._foreach_zero_(list(self.grads.values()))
         nn.head(self.feat, ch[0], P0, self.params["head.w"], self.params["head.b"], target, weight, mask, err, dz,
                 loss, P0)
         d = self._buf("gdec0b", (B, H, W, ch[0]))
