@@ -531,7 +531,10 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
         v[2 * k + 1] = make_float2(yy.z, yy.w);
       }
     };
-    constexpr bool TWREG = !FOLDED && !LEAN;                       // a column's twiddles in registers for the bin
+    // A column's twiddles stay in registers for the bin, also where a few spill (24 at 32 lateral
+    // samples: 152 us against 163 for 16 frames with them read at their use; 64: 281 / 299; 416:
+    // 3029 / 3160; 448 even).  With 15 points in stage 3 69 spill and reading them wins: 3452 -> 3230.
+    constexpr bool TWREG = !FOLDED && !LEAN && (NSUB < 3 || K < 15);
     float2 tw[TWREG ? 16 : 1];
     if constexpr (TWREG) {
 #pragma unroll
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
 #pragma unroll
         for (int x1 = k1; x1 < 16; x1 += 4) {
           if constexpr (FOLDED) put2(tcol + x1 * kFfRow, p[i][x1]);
-          else if constexpr (LEAN) put2(tcol + x1 * kFfRow, twiddled(p[i][x1], get2(twj + x1 * 16)));
+          else if constexpr (!TWREG) put2(tcol + x1 * kFfRow, twiddled(p[i][x1], get2(twj + x1 * 16)));
           else put2(tcol + x1 * kFfRow, x1 == 0 ? p[i][x1] : twiddled(p[i][x1], tw[x1]));
         }
         if constexpr (SPREAD) __builtin_amdgcn_sched_barrier(0);
