@@ -132,7 +132,9 @@ __global__ __launch_bounds__(256, 2) void conv3x3_kernel(ConvArgs a) {
     put(w_now);
     __syncthreads();
     if (it + 1 < n_items) fetch(it + 1, nch > 1);
-#pragma unroll 1
+    // taps unrolled so that a tap's operand reads run ahead of the products before it: all nine where the
+    // accumulators leave room, three (a row) where nine spill (32 -> 32 channels of 8 x 512 x 256: 52 us against 49)
+#pragma unroll (RW * NO > 2 ? 3 : 9)
     for (int t = 0; t < 9; ++t) {
       int dh = t / 3 - 1, dw = t % 3 - 1;
       if (a.flip) {
@@ -925,6 +927,17 @@ inline bool vec8(int c, int ld_a, int ld_b, const void* a, const void* b) {
   return c % 8 == 0 && ld_a % 8 == 0 && ld_b % 8 == 0 && aligned16(a) && aligned16(b);
 }
 
+// (the kernel attribute for LDS beyond 64 KB is set before each launch)
+template <int RW, int NO>
+pam_status_t launch_conv(const ConvArgs& a, dim3 grid, hipStream_t st) {
+  if (conv_lds_bytes<RW, NO>() > 65536 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(conv3x3_kernel<RW, NO>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, conv_lds_bytes<RW, NO>()) != hipSuccess)
+    return PAM_ERR_DEVICE;
+  hipLaunchKernelGGL((conv3x3_kernel<RW, NO>), grid, dim3(256), (conv_lds_bytes<RW, NO>()), st, a);
+  return launched();
+}
+
 }  // namespace
 
 extern "C" {
@@ -940,28 +953,29 @@ pam_status_t pam_nn_conv3x3(const void* x, int32_t ldx, int32_t batch, int32_t h
              w, k_in, ldy, n_out, relu, flip, accumulate, 0, w / 32, 0, 1};
   // 64 output channels x 8 rows per tile where the channels allow, else 32 x 16; runs of
   // up to 8 tiles per workgroup, as long as about 512 workgroups (two per CU, the LDS
-  // limit) remain
+  // limit) remain.  A layer with less than two workgroups per CU that way is bound by the
+  // serial chain of its chunks, so it takes tiles of half the rows, and one with less than
+  // half a workgroup per CU 32 channels x 4 rows.  256 -> 256 channels of 32-pixel rows: 8 x 64
+  // rows 35 -> 34 us, 4 x 64 32 -> 25, 1 x 64 30 -> 19; 32 -> 32 of 512 x 256 11.5 -> 9.5; with 4-row
+  // tiles from 512 workgroups up (128 -> 128 of 8 x 128 x 64) 30 -> 37.  A pixel's sum keeps its order.
   const bool wide = n_out % 64 == 0;
-  const int rows = wide ? 8 : 16, groups = n_out / (wide ? 64 : 32);
+  const auto tiles_of = [&](int rows) { return (int64_t)batch * ((h + rows - 1) / rows) * (w / 32); };
+  int rows = wide ? 8 : 16, ch = wide ? 64 : 32;
+  const int64_t full = tiles_of(rows) * (n_out / ch);
+  if (full < 512) rows /= 2;
+  if (full < 128) rows = 4, ch = 32;
   a.n_rt = (h + rows - 1) / rows;
-  const int64_t tiles = (int64_t)batch * a.n_rt * a.n_ct;
+  const int64_t tiles = tiles_of(rows);
   if (tiles > 0x7fffffffLL) return PAM_ERR_INVALID_ARG;
+  const int groups = n_out / ch;
   a.n_tiles = (int)tiles;
   a.run = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * groups / 512));
   const dim3 grid((unsigned)((tiles + a.run - 1) / a.run), groups);
-  // (more than 64 KB of LDS: the kernel attribute is set before each launch)
-  if (wide) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(conv3x3_kernel<2, 2>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, conv_lds_bytes<2, 2>()) != hipSuccess)
-      return PAM_ERR_DEVICE;
-    hipLaunchKernelGGL((conv3x3_kernel<2, 2>), grid, dim3(256), (conv_lds_bytes<2, 2>()), st, a);
-  } else {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(conv3x3_kernel<4, 1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, conv_lds_bytes<4, 1>()) != hipSuccess)
-      return PAM_ERR_DEVICE;
-    hipLaunchKernelGGL((conv3x3_kernel<4, 1>), grid, dim3(256), (conv_lds_bytes<4, 1>()), st, a);
-  }
-  return launched();
+  if (rows == 8 && ch == 64) return launch_conv<2, 2>(a, grid, st);
+  if (rows == 8) return launch_conv<2, 1>(a, grid, st);
+  if (rows == 4 && ch == 64) return launch_conv<1, 2>(a, grid, st);
+  if (rows == 4) return launch_conv<1, 1>(a, grid, st);
+  return launch_conv<4, 1>(a, grid, st);
 }
 
 pam_status_t pam_nn_conv3x3_wgrad(const void* x, int32_t ldx, const void* dy, int32_t lddy, int32_t batch, int32_t h,

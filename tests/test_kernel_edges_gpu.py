@@ -250,3 +250,33 @@ def test_fd_tea_shapes(env, L, n_x, n_sub, kw):
     for f in range(2):
         assert rel(img[f].double().cpu().numpy(), ref["I"]) <= 1e-5
         assert np.abs(nncc[f].double().cpu().numpy() - ref["rho_n"]).max() <= 1e-4
+
+
+# Operands in {-1, 0, 1}: every partial sum is a small integer, exact in FP32 in any order, so the result is the
+# exact sum rounded once to BF16 and has to match bit for bit.
+@pytest.mark.parametrize("B,h,w,k_in,n_out,acc", [
+    (2, 131, 512, 32, 64, False),    # 544 workgroups of 8 rows x 64 channels: full tiles, several per workgroup
+    (2, 245, 512, 32, 32, True),     # 512 of 16 rows x 32 channels, ragged rows
+    (2, 37, 256, 64, 128, False),    # 160: tiles of 4 rows x 64 channels
+    (1, 253, 128, 32, 64, True),     # 128, the first of that form, one row short of a tile
+    (2, 53, 128, 64, 160, False),    # 160: tiles of 8 rows x 32 channels
+    (1, 248, 128, 32, 64, False),    # 124, the last of the smallest form
+    (1, 124, 256, 64, 32, True),     # 64: tiles of 4 rows x 32 channels
+    (1, 3, 32, 64, 64, False),       # one tile, fewer rows than it has
+])
+def test_conv3x3_tile_forms(env, B, h, w, k_in, n_out, acc):
+    """The 3x3 convolution at each tile form its dispatch chooses by the number of tiles."""
+    torch, nn = env
+    rng = np.random.default_rng(h * w + n_out)
+    x, xd = bf16(torch, rng.integers(-1, 2, (B, h, w, k_in)))
+    wt, wd = bf16(torch, rng.integers(-1, 2, (n_out, 9, k_in)))
+    y0, y = bf16(torch, rng.integers(-8, 9, (B, h, w, n_out)))
+    b = rng.integers(-8, 9, n_out).astype(np.float32)
+    bd = None if acc else torch.from_numpy(b).cuda()
+    nn.conv3x3(xd, k_in, B, h, w, k_in, wd, bd, y, n_out, n_out, relu=not acc, accumulate=acc)
+    xp = np.pad(x, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    want = np.zeros((B, h, w, n_out))
+    for t in range(9):
+        want += xp[:, t // 3:t // 3 + h, t % 3:t % 3 + w] @ wt[:, t].T
+    want = want + y0 if acc else np.maximum(want + b, 0.0)
+    assert np.array_equal(y.double().cpu().numpy(), bf16(torch, want)[0])
