@@ -122,8 +122,8 @@ typedef struct {
 /* Where each stage's result lies inside a workspace (byte offsets), for callers
  * that check intermediate results.  Layouts (all row-major, last index fastest):
  *   spectra  complex64 [F][n_sel][L]          time-transform bins, Omega order
- *   coeffs   complex64 [F][n_sel][n_sub][N_x] lateral coefficients: at N_x = 256 and 512
- *            (and 128 with FP32 operands) the spectrum P_i(q)/N_x stored at r*16 + q1 for
+ *   coeffs   complex64 [F][n_sel][n_sub][N_x] lateral coefficients: with FP32 operands, and
+ *            at N_x = 256 and 512 in every form, the spectrum P_i(q)/N_x stored at r*16 + q1 for
  *            q = (N_x/16) q1 + r (factored transform), otherwise folded into cos/sin slot
  *            order; scaled by a power of two for FP16 operands (scale 1 otherwise)
  *   scales   float32   [F][n_sel]             1 / (power-of-two scale of coeffs)

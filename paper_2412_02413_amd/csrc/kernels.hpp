@@ -3,16 +3,19 @@
 //   k1_time_fft   F_t of every channel (Eq. 1): real FFT of n_t samples as an
 //                 n_t/2-point complex Stockham FFT (radix 8) in LDS, then the in-band bins.
 //   k2_lateral    apodization (Pattern-m masks) + lateral DFT F_x (Eq. 1) per
-//                 (frame, bin), folded into the coefficients of a real DFT basis.
-//   k3_fields     the propagator exp(i z kz) of Eq. 2 (FP64 phase, FP32 sin/cos)
-//                 times the folded coefficients, the inverse lateral transform as
-//                 a GEMM against a fixed real cos/sin basis on the matrix cores,
-//                 and the sums over frequency of |p_i|^2 and Re(p_i^* p_j)
-//                 (Eq. 4, Eq. 11) kept in registers.  Fields are never stored.
+//                 (frame, bin), folded into the coefficients of a real DFT basis: the
+//                 16-bit forms at lateral sizes other than 256 and 512 (k2_fft serves
+//                 every other plan).
+//   k3_fields     the same plans' fields: the propagator exp(i z kz) of Eq. 2 (FP64
+//                 phase, FP32 sin/cos) times the folded coefficients, the inverse
+//                 lateral transform as a GEMM against a fixed real cos/sin basis on the
+//                 matrix cores, and the sums over frequency of |p_i|^2 and
+//                 Re(p_i^* p_j) (Eq. 4, Eq. 11) kept in registers.  Fields are never
+//                 stored.  FP32 plans take k3fft, the other 16-bit ones k3ff.
 //   k4_weight     NCC pairs, eps floor, TAX cube root (Eq. 10), energy, per-block max.
 //   k4_image      NNCC normalisation and I = rho_n^2 E (Eq. 11).
 //
-// Folding.  The propagator depends on kx only through kx^2, so H(q) = H(N-q) on
+// Folding (k2_lateral, k3_fields).  The propagator depends on kx only through kx^2, so H(q) = H(N-q) on
 // the DFT grid.  Pairing q with N-q turns the inverse transform
 //     p(x) = (1/N) sum_q H(q) P(q) e^{+2 pi i q x / N}
 // into a sum over N real basis functions, cos(2 pi q x/N) for q = 0..N/2 and
