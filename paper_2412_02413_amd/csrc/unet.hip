@@ -551,10 +551,12 @@ __global__ void upsample8_bwd_kernel(const bf16* dy, int32_t lddy, int64_t n8, i
 // pixel; with the loss, a grid-stride loop of at most 256 workgroups of 1024 threads (one per CU, the chip's wave
 // slots half full), since every workgroup ends in three atomics on the same cache line and those are serialised: one
 // workgroup per 256 pixels (12,288 atomics at 8 x 512 x 256 pixels) took
-// 167 us there, this 27 us (18 us without the loss).
+// 167 us there, this 24 us (18 us without the loss).  w and b are __restrict__ so that the stores of one pixel do not
+// send the next one's weights through vector loads instead of scalar ones (27 us, and 16 frames of mask and error 41 against 33).
 template <bool LOSS>
-__global__ __launch_bounds__(LOSS ? 1024 : 256) void head_kernel(const bf16* feat, int32_t c, int64_t P, const float* w,
-                                                                 const float* b, const float* target,
+__global__ __launch_bounds__(LOSS ? 1024 : 256) void head_kernel(const bf16* __restrict__ feat, int32_t c, int64_t P,
+                                                                 const float* __restrict__ w,
+                                                                 const float* __restrict__ b, const float* target,
                                                                  const float* weight, float* mask, float* err,
                                                                  float* dz, float* loss, float inv_count) {
   float l0 = 0.f, l1 = 0.f, l2 = 0.f;
