@@ -868,18 +868,29 @@ __global__ __launch_bounds__(256) void coherence_features_kernel(const float* ac
 
 // Predicted relative L2 error of a frame's image: with the image mask^2 E and a mask
 // off by err per pixel, the image error is about 2 mask err E, so
-// est = ||2 mask err E|| / ||mask^2 E|| (sums in FP64).
+// est = ||2 mask err E|| / ||mask^2 E|| (sums in FP64).  One workgroup a frame, bound by the latency of its loads:
+// eight pixels a thread are loaded before they are added (in the same order), 66 -> 31 us for 16 frames of 512 x 256
+// fresh from the network.
 __global__ __launch_bounds__(1024) void error_estimate_kernel(const float* mask, const float* err, const float* E,
                                                               int64_t P, float* est) {
   __shared__ double s0[1024], s1[1024];
   const int64_t f = blockIdx.x;
   double a = 0.0, b = 0.0;
-  for (int64_t p = threadIdx.x; p < P; p += 1024) {
-    const double m = mask[f * P + p], e = E[f * P + p];
-    const double d = 2.0 * m * (double)err[f * P + p] * e, i = m * m * e;
+  const auto add = [&](double m, double r, double e) {
+    const double d = 2.0 * m * r * e, i = m * m * e;
     a += d * d;
     b += i * i;
+  };
+  const float *mf = mask + f * P, *rf = err + f * P, *ef = E + f * P;
+  int64_t p = threadIdx.x;
+  for (; p + 7 * 1024 < P; p += 8 * 1024) {
+    float m[8], r[8], e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m[j] = mf[p + 1024 * j], r[j] = rf[p + 1024 * j], e[j] = ef[p + 1024 * j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) add(m[j], r[j], e[j]);
   }
+  for (; p < P; p += 1024) add(mf[p], rf[p], ef[p]);
   s0[threadIdx.x] = a;
   s1[threadIdx.x] = b;
   __syncthreads();

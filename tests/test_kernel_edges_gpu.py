@@ -280,3 +280,18 @@ def test_conv3x3_tile_forms(env, B, h, w, k_in, n_out, acc):
         want += xp[:, t // 3:t // 3 + h, t % 3:t % 3 + w] @ wt[:, t].T
     want = want + y0 if acc else np.maximum(want + b, 0.0)
     assert np.array_equal(y.double().cpu().numpy(), bf16(torch, want)[0])
+
+
+# The kernel sums FP64 products of the FP32 inputs, so what is left is the one rounding of the result to FP32
+# (2^-24) and the FP64 sums' own rounding.
+@pytest.mark.parametrize("pixels", [1, 1025, 7 * 1024 + 1, 8 * 1024 - 1, 8 * 1024, 8 * 1024 + 3, 17 * 1024 + 5])
+def test_error_estimate_lengths(env, pixels):
+    """The predicted image error around the lengths where its batched loads begin and end."""
+    torch, nn = env
+    rng = np.random.default_rng(pixels)
+    m, r, e = (rng.random((2, pixels)).astype(np.float32) for _ in range(3))
+    est = torch.empty(2, device="cuda")
+    nn.error_estimate(*(torch.from_numpy(v).cuda() for v in (m, r, e)), 2, pixels, est)
+    m, r, e = (v.astype(np.float64) for v in (m, r, e))
+    want = np.linalg.norm(2 * m * r * e, axis=1) / np.linalg.norm(m * m * e, axis=1)
+    np.testing.assert_allclose(est.double().cpu().numpy(), want, rtol=2.0 ** -23)
