@@ -46,6 +46,7 @@ struct TeaArgs {
   double dx;               // grid spacing
   double cyc;              // fs / (n_t c): phase cycles per bin index per metre of path
   int32_t L, N, n_z, n_sel, F, n_split, bins_per_split;
+  int32_t n_acc;           // accumulator planes per frame: more than this kernel writes on a plan with pair sums
   int32_t col0, step;      // grid column of element l: col0 + step l
   // the split of a depth's pixels into lanes (tea_shape)
   int32_t T, Q, rows, chunks, PL, n_wg;
@@ -221,10 +222,9 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
     }
   }
   if (!lane_live) return;
-  constexpr int NA = AccCount<NSUB>::total;
   const size_t plane = (size_t)a.n_z * a.N;
   const int row = row0 + slot;
-  float* dst = a.accum + ((size_t)sp * a.F + f) * NA * plane + (size_t)(row / a.step) * a.N + row % a.step;
+  float* dst = a.accum + ((size_t)sp * a.F + f) * a.n_acc * plane + (size_t)(row / a.step) * a.N + row % a.step;
 #pragma unroll
   for (int i = 0; i < TEA_PX; ++i) {
     if (t0 + i >= a.T || row % a.step + a.step * (t0 + i) >= a.N) continue;

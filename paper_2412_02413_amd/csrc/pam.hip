@@ -1119,6 +1119,7 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
       a.F = q.F;
       a.n_split = q.s.n_split;
       a.bins_per_split = q.s.bins_per_split;
+      a.n_acc = n_acc(p->n_sub, p->coherence);
       a.col0 = p->col0;
       a.step = p->col_step;
       pam::tea_shape(a);

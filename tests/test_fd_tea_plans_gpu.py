@@ -1,0 +1,57 @@
+"""FD-TEA-TAX on every kind of plan that accepts it, against the FP64 oracle (relative L2 of the
+image <= 1e-5, absolute NNCC error <= 1e-4, as for the FP32 path everywhere)."""
+import numpy as np
+import pytest
+
+from oracle import fd_tea as T
+from paper_2412_02413_amd import synth
+
+pytestmark = pytest.mark.gpu
+MM = 1e-3
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2412_02413_amd import pam
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pam._lib()
+    return torch, pam
+
+
+def check_fd_tea(env, g, frames, seed):
+    """Frames of different content through a workspace that holds NaN wherever the call does not
+    write: a partial sum read from a place that was not written shows in the image."""
+    torch, pam = env
+    rng = np.random.default_rng(seed)
+    rf = np.stack([synth.render(g, [synth.Emitter((0.4 * f - 0.5) * MM, (14 + f) * MM, "broadband")], rng, snr_db=20.0)
+                   for f in range(frames)])
+    plan = pam.pam_plan(g, 0, "fp32")
+    try:
+        img = torch.full((frames, plan.n_z, plan.n_x), -1.0, device="cuda")
+        nncc = torch.full_like(img, -1.0)
+        ws = pam.alloc_workspace(plan, frames, g.n_samples).fill_(255)
+        pam.pam_fd_tea_tax(plan, torch.from_numpy(rf).cuda(), img, nncc, None, ws)
+        torch.cuda.synchronize()
+        n_split = pam.pam_workspace_layout(plan, frames, g.n_samples).n_split
+    finally:
+        pam.pam_destroy(plan)
+    for f in range(frames):
+        ref = T.fd_tea_tax(rf[f], g)
+        I, rho = img[f].double().cpu().numpy(), nncc[f].double().cpu().numpy()
+        e_i = float(np.linalg.norm(I - ref["I"]) / np.linalg.norm(ref["I"]))
+        e_r = float(np.abs(rho - ref["rho_n"]).max())
+        print(f"frame {f}: relL2(I)={e_i:.2e} max|d rho_n|={e_r:.2e}", flush=True)
+        assert e_i <= 1e-5 and e_r <= 1e-4
+    return n_split
+
+
+@pytest.mark.parametrize("frames,bins_hi", [(1, 9e6), (2, 9e6), (2, 2.5e6)])
+def test_plan_with_pair_sums(env, frames, bins_hi):
+    """A coherence plan keeps five accumulator planes a frame, of which delay-and-sum writes the
+    first: several frames and several bin splits have to land where the weight step reads them."""
+    g = synth.Geometry(n_elements=32, pitch_m=0.3 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=512,
+                       bands_hz=[(2e6, bins_hi)], depths_m=(12 + 0.5 * np.arange(14)) * MM, n_x=256, n_sub=1,
+                       apod=np.ones((1, 32), np.uint8), coherence=1)
+    n_split = check_fd_tea(env, g, frames, 5)
+    assert n_split > 1
