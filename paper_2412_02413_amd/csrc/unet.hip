@@ -249,6 +249,19 @@ __device__ __forceinline__ v8bf pixels8(const bf16* at) {
   return __builtin_shufflevector(l, u, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The first n of eight pixels, zeros in the place of the others.
+__device__ __forceinline__ v8bf first_pixels(v8bf v, int n) {
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  v4u w = __builtin_bit_cast(v4u, v);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] &= n > 2 * k + 1 ? 0xFFFFFFFFu : (n > 2 * k ? 0xFFFFu : 0u);
+  return __builtin_bit_cast(v8bf, w);
+}
+
+// EDGE: tiles reach past the image (h not a multiple of 8 or w not of 32).  A pixel that does not exist has dy = 0, but
+// x beside it is real, and an Inf or NaN there times 0 would be NaN in a tap that never sees it; so x is cleared there
+// too, with masks over the operand (a branch around the products spilled the accumulators: 42 -> 550 us).
+template <bool EDGE>
 __global__ __launch_bounds__(kWgThreads, 2) void wgrad_kernel(WgradArgs a) {
   extern __shared__ __align__(16) bf16 lds_w[];          // [2][x pixels, dy pixels][32]
   const int c0 = blockIdx.x * 32, o0 = blockIdx.y * 32;
@@ -311,12 +324,15 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_kernel(WgradArgs a) {
     if (tile + 1 < t_end) fetch(tile + 1);
     const bf16* xs = cur + (wv * 34 + tr_pix) * 32 + tr_ch;            // tap (0, 0) of pixel column 0
     const bf16* ds = cur + (kWgXPix + wv * 32 + tr_pix) * 32 + tr_ch;
+    // pixels of the wave's row that exist in this tile (EDGE)
+    const int cols = EDGE && (tile / a.n_ct) % a.n_rt * kWgRows + wv < a.h ? a.w - tile % a.n_ct * 32 : 0;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const v8bf bv = pixels8(ds + 16 * s * 32);
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
-        const v8bf av = pixels8(xs + ((t / 3) * 34 + t % 3 + 16 * s) * 32);
+        v8bf av = pixels8(xs + ((t / 3) * 34 + t % 3 + 16 * s) * 32);
+        if constexpr (EDGE) av = first_pixels(av, cols - 16 * s - 8 * half);
         C[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, C[t], 0, 0, 0);
       }
       if (bias) B = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, bv, B, 0, 0, 0);
@@ -1015,11 +1031,12 @@ pam_status_t pam_nn_conv3x3_wgrad(const void* x, int32_t ldx, const void* dy, in
   }
   a.run = (int)((tiles + best - 1) / best);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          kWgLds) != hipSuccess)
+  const auto kernel = h % kWgRows || w % 32 ? wgrad_kernel<true> : wgrad_kernel<false>;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kWgLds) !=
+      hipSuccess)
     return PAM_ERR_DEVICE;
-  hipLaunchKernelGGL(wgrad_kernel, dim3(c_in / 32, c_out / 32, (unsigned)((tiles + a.run - 1) / a.run)),
-                     dim3(kWgThreads), kWgLds, st, a);
+  hipLaunchKernelGGL(kernel, dim3(c_in / 32, c_out / 32, (unsigned)((tiles + a.run - 1) / a.run)), dim3(kWgThreads),
+                     kWgLds, st, a);
   return launched();
 }
 
