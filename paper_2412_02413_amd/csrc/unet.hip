@@ -236,7 +236,7 @@ constexpr int kWgBuf = (kWgXPix + kWgDPix) * 32;         // BF16 per LDS buffer
 constexpr int kWgLds = 2 * kWgBuf * 2;                   // bytes (two buffers)
 constexpr int kWgXPieces = (kWgXPix * 4 + kWgThreads - 1) / kWgThreads;   // 16-byte pieces per thread
 constexpr int kWgDPieces = kWgDPix * 4 / kWgThreads;
-static_assert(kWgDPix * 4 % kWgThreads == 0 && kWgThreads * 16 * 4 <= kWgLds, "wgrad tile");
+static_assert(kWgDPix * 4 % kWgThreads == 0 && 2 * kWgRows * 1024 * 4 <= kWgLds, "wgrad tile");
 
 // 8 pixels p, p + 1, ..., p + 7 of one channel per lane from LDS rows of 32 channels: `at`
 // addresses the lane's 8-byte piece of pixel p + r (r = lane % 16 / 4).
@@ -341,9 +341,12 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_kernel(WgradArgs a) {
     __syncthreads();
   }
   // C[t][v] holds (c = 8 (v / 4) + 4 half + v % 4, o = i)
-  float* red = reinterpret_cast<float*>(lds_w);            // [8 waves][32 c][32 o], no reads pending
+  // [8 waves][32 c][32 o] per tap, no reads pending; alternate taps use alternate halves, so that one barrier a tap is
+  // enough (a tap's sums are read before the next barrier, and its half is written again after that one)
+  float* const red2 = reinterpret_cast<float*>(lds_w);
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
+    float* red = red2 + (t & 1) * kWgRows * 1024;
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[(wv * 32 + 8 * (v >> 2) + 4 * half + (v & 3)) * 32 + i] = C[t][v];
     __syncthreads();
@@ -353,9 +356,9 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_kernel(WgradArgs a) {
       for (int k = 0; k < kWgRows; ++k) sum += red[1024 * k + e];
       atomicAdd(a.dw + ((int64_t)t * a.c_in + c0 + (e >> 5)) * a.c_out + o0 + (e & 31), sum);
     }
-    __syncthreads();
   }
   if (bias) {                                              // every row of B is the column sum
+    float* red = red2 + kWgRows * 1024;                    // the ninth tap's sums are in the other half
     if (half == 0) red[wv * 32 + i] = B[0];
     __syncthreads();
     if (tid < 32) {
