@@ -516,28 +516,38 @@ struct K4Args {
   double eps;
 };
 
-// 1 / sqrt(x) in FP64 for x > 0 (one Newton step on the hardware's estimate of about 2^-26: 2^-50; 0 for infinity).
+// 1 / sqrt(x) in FP64 for x > 0, 0 for infinity: two Newton steps on the hardware's estimate, which is good to 2^-23 at
+// least (2^29 ulp): 2^-45, then 2^-90, so what is left is rounding.  x y rounds once (2^-54 of the result), the last FMA
+// once (2^-53).  An NCC cc rsqrt_pos(S_i S_j) so carries 3 x 2^-53 at most, where two square roots, their product and a
+// division carry 4 x 2^-53.
 __device__ __forceinline__ double rsqrt_pos(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  return x < __builtin_huge_val() ? fma(0.5 * y, fma(-x * y, y, 1.0), y) : 0.0;
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return x < __builtin_huge_val() ? y : 0.0;
 }
 
-// cbrt(a) for 0 < a <= 1 in FP64, accurate to about 1e-12: one Newton step of t <- t (4 - a t^3) / 3 for
-// t = a^(-1/3) from the FP32 hardware log2 / exp2, then a t^2.  Values whose FP32 image is not normal take cbrt().
+// cbrt(a) for 0 < a <= 1 in FP64, to 0.51 ulp: t = a^(-1/3) from the FP32 hardware log2 / exp2 (within 4e-6 for
+// a >= 1e-36), one Newton step u = t (4 - a t^3) / 3 (3e-11), c = a u^2, and a last Newton step on c itself with the
+// residual a - c^3 formed exactly enough by FMAs; 1 / 3 c^2 = u^2 / 3 there.  Values whose FP32 image is not normal take
+// cbrt().
 __device__ __forceinline__ double cbrt_unit(double a) {
   if (!(a > 1e-36)) return cbrt(a);
   const double t = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)a) * (-1.0f / 3.0f));
   const double e = fma(-a * t, t * t, 1.0);          // 1 - a t^3
-  const double u = fma(t * (1.0 / 3.0), e, t);
-  return a * u * u;
+  const double u = fma(t * (1.0 / 3.0), e, t), u2 = u * u;
+  const double c = a * u2, c2 = c * c;
+  const double res = fma(-c2, c, a) - fma(c, c, -c2) * c;   // a - c^3
+  return fma(res * (1.0 / 3.0), u2, c);
 }
 
 // The bin splits' partial sums of a pixel added in FP64, then NCC, weight and energy.  A workgroup covers 256 pixels
 // of one frame with SG threads a pixel: thread group sg adds splits sg, sg + SG, ... of every channel and the groups
 // meet in LDS, so that many splits are not one serial chain of loads.  Bound by reading the partial sums (at 64 frames
 // of one split also by the FP64 arithmetic, hence the Newton forms above).  One thread a pixel with run-time channel
-// loops and library sqrt, division and cbrt took 42 us for 19,328 pixels of 26 splits (now 5.0), 31 us for 131,072 of
-// 16 (now 10.5: 50 MB at 4.8 TB/s) and 98 us for 64 frames of 131,072 of one split (now 54: 268 MB at 5.0 TB/s).
+// loops and library sqrt, division and cbrt took 42 us for 19,328 pixels of 26 splits (this 7.0 for 52), 31 us for 131,072 of
+// 16 (now 10.1: 50 MB at 5.0 TB/s) and 95 us for 64 frames of 131,072 of one split (now 56: 268 MB at 4.8 TB/s; 52 with
+// one Newton step each, which left errors of 2^-45 and 3e-11).
 template <int NSUB, int SG>
 __global__ __launch_bounds__(256 * SG) void k4_weight(K4Args a) {
   constexpr int NP = AccCount<NSUB>::pairs, NR = AccCount<NSUB>::total;   // pairs and channels read here
