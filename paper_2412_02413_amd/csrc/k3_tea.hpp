@@ -235,4 +235,70 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
   }
 }
 
+// Few elements: one thread a pixel makes its own phasors, with the delays in registers.  A row's table holds 4 PL phasors
+// however few pixels and elements the row has, so below some number of elements it costs more than it saves: of
+// 4 frames of 151 x 512 pixels and 205 bins, one element zero-stuffed takes 674 us with the table (12 phasors for each
+// one-pixel row) and 79 here, two 376 and 112, four 231 and 175, eight 232 and 313; padded (rows of 512 pixels in two
+// tables of 264) two take 129 and 110, three 134 and 142.  At 32 to 512 columns the two meet where a depth's pixels
+// times elements are about 2.8 of its table phasors, which tea_few takes as the line; at most six elements get there.
+constexpr int kTeaFew = 6;
+inline bool tea_few(const TeaArgs& a) {              // (a's shape set)
+  return a.L <= kTeaFew && 5ll * a.L * a.N <= 14ll * a.step * a.chunks * 4 * a.PL;
+}
+template <int NSUB>
+__global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea_few(TeaArgs a) {
+  constexpr int NP = AccCount<NSUB>::pairs;
+  int bid = blockIdx.x;
+  const int sp = bid % a.n_split; bid /= a.n_split;
+  const int wg = bid % a.n_wg; bid /= a.n_wg;
+  const int f = bid;
+  const int b_begin = sp * a.bins_per_split;
+  const int b_end = min(a.n_sel, b_begin + a.bins_per_split);
+  const int n_pix = a.n_z * a.N, pix = wg * 64 * TEA_WAVES + (int)threadIdx.x;
+  const int d = min(pix, n_pix - 1) / a.N, j = min(pix, n_pix - 1) - d * a.N;
+  const int code = *(const scalar_int*)a.units;                     // membership bits of the one unit
+  double u[kTeaFew];
+#pragma unroll
+  for (int l = 0; l < kTeaFew; ++l) {
+    const double x = (double)(j - a.col0 - a.step * l) * a.dx, z = a.z[d];
+    u[l] = l < a.L ? sqrt(x * x + z * z) * a.cyc : 0.0;
+  }
+  float accS[NSUB], accC[NP > 0 ? NP : 1];
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) accS[s] = 0.f;
+#pragma unroll
+  for (int c = 0; c < (NP > 0 ? NP : 1); ++c) accC[c] = 0.f;
+  for (int b = b_begin; b < b_end; ++b) {
+    const double k = (double)a.ksel[b];
+    const scalar_float* X = (const scalar_float*)(a.spectra + ((size_t)f * a.n_sel + b) * a.L);
+    float2 p[NSUB];
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) p[s] = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int l = 0; l < kTeaFew; ++l) {
+      if (l >= a.L) break;
+      const double ph = k * u[l];
+      const float r = (float)(ph - rint(ph));
+      const float2 v = cmul(make_float2(X[2 * l], X[2 * l + 1]),
+                            make_float2(__builtin_amdgcn_cosf(r), __builtin_amdgcn_sinf(r)));
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+        if (code >> (3 * l + s) & 1) p[s] = cadd(p[s], v);
+    }
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) accS[s] = fmaf(p[s].x, p[s].x, fmaf(p[s].y, p[s].y, accS[s]));
+#pragma unroll
+    for (int c = 0; c < NP; ++c) {
+      const float2 v = p[c], w = p[NSUB == 3 ? (c + 1) % 3 : 1];
+      accC[c] = fmaf(v.x, w.x, fmaf(v.y, w.y, accC[c]));
+    }
+  }
+  if (pix >= n_pix) return;
+  float* dst = a.accum + ((size_t)sp * a.F + f) * a.n_acc * n_pix + pix;
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) dst[(size_t)s * n_pix] = accS[s];
+#pragma unroll
+  for (int c = 0; c < NP; ++c) dst[(size_t)(NSUB + c) * n_pix] = accC[c];
+}
+
 }  // namespace pam

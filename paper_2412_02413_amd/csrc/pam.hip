@@ -1123,12 +1123,17 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
       a.col0 = p->col0;
       a.step = p->col_step;
       pam::tea_shape(a);
+      const bool few = pam::tea_few(a);
+      if (few) a.n_wg = (pix + 64 * pam::TEA_WAVES - 1) / (64 * pam::TEA_WAVES);
       const long long blocks = (long long)q.F * a.n_wg * q.s.n_split;
       if (blocks > 0x7fffffffLL) return PAM_ERR_UNSUPPORTED;
-      const size_t lds = pam::tea_lds(a);
+      const size_t lds = few ? 0 : pam::tea_lds(a);
       const dim3 grid((unsigned)blocks), block(64 * pam::TEA_WAVES);
       auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, lds, stream, a); };
-      switch (2 * p->n_sub + p->mixed_units) {
+      switch (few ? -p->n_sub : 2 * p->n_sub + p->mixed_units) {
+        case -3: launch(pam::k3_tea_few<3>); break;
+        case -2: launch(pam::k3_tea_few<2>); break;
+        case -1: launch(pam::k3_tea_few<1>); break;
         case 7: launch(pam::k3_tea<3, true>); break;
         case 6: launch(pam::k3_tea<3, false>); break;
         case 5: launch(pam::k3_tea<2, true>); break;

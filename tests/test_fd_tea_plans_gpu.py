@@ -55,3 +55,22 @@ def test_plan_with_pair_sums(env, frames, bins_hi):
                        apod=np.ones((1, 32), np.uint8), coherence=1)
     n_split = check_fd_tea(env, g, frames, 5)
     assert n_split > 1
+
+
+@pytest.mark.parametrize("L,n_x,lateral,n_sub,kw", [
+    (1, 32, "pad", 1, {}),                                    # one thread a pixel from here ...
+    (1, 512, "stuff", 2, {}),
+    (2, 96, "stuff", 3, {"pattern_m": 1}),
+    (2, 512, "pad", 3, {"pattern_m": 1}),
+    (4, 64, "stuff", 3, {"apod": np.uint8([[1, 1, 0, 0], [0, 1, 1, 0], [0, 1, 0, 1]])}),   # in several and in none
+    (5, 288, "pad", 3, {"pattern_m": 2}),
+    (6, 480, "stuff", 2, {"pattern_m": 2}),                   # ... to the most it takes
+    (3, 512, "pad", 3, {"pattern_m": 1}),                     # the table's first
+    (7, 224, "stuff", 3, {"pattern_m": 2}),
+    (8, 32, "stuff", 3, {"pattern_m": 2}),
+])
+def test_few_elements(env, L, n_x, lateral, n_sub, kw):
+    """Both sides of the line between one thread a pixel and the phasor table; 11 depths leave a ragged last tile."""
+    g = synth.Geometry(n_elements=L, pitch_m=0.3 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=128, bands_hz=[(2e6, 6e6)],
+                       depths_m=(12 + 0.7 * np.arange(11)) * MM, n_x=n_x, n_sub=n_sub, lateral=lateral).replace(**kw)
+    check_fd_tea(env, g, 2, L + n_x)
