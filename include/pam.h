@@ -58,7 +58,7 @@ typedef enum {
   PAM_ERR_OOM = -2,         /* device or host allocation failed (pam_plan only) */
   PAM_ERR_DEVICE = -3,      /* a HIP runtime call or kernel launch failed */
   PAM_ERR_UNSUPPORTED = -4, /* valid but outside what the kernels handle (sizes) */
-  PAM_ERR_WORKSPACE = -5    /* workspace null or smaller than pam_workspace_size */
+  PAM_ERR_WORKSPACE = -5    /* workspace null or too small (pam_workspace_layout_in) */
 } pam_status_t;
 
 /* How the L physical channels are laid on the N_x-column lateral grid. */
@@ -73,7 +73,7 @@ typedef enum {
  * propagator phase z*kz and its reduction modulo 2 pi are FP64 in every mode,
  * the sine/cosine FP32; all accumulations are FP32; NCC denominators FP64. */
 typedef enum {
-  PAM_PREC_FP32 = 0,       /* FP32 operands, FP32 matrix-core products                */
+  PAM_PREC_FP32 = 0,       /* FP32 operands, FFT on the vector units                  */
   PAM_PREC_SPLIT_BF16 = 1, /* operands split hi+lo in BF16, three BF16 products       */
   PAM_PREC_SPLIT_FP16 = 2, /* operands split hi+lo in FP16 (power-of-two pre-scaled)  */
   PAM_PREC_BF16 = 3,       /* single BF16 product                                     */
@@ -160,10 +160,21 @@ pam_status_t pam_plan_get_bins(pam_plan_t p, int32_t* bins, int32_t capacity);
  * splits each frame's bins into n_split ranges (chosen per call from the frames, the
  * bins and how many fields workgroups the device holds at once); the accum region
  * reserves n_frames plus a fixed number of spare planes, enough for any split the
- * library picks. */
+ * library picks.
+ *   A call given less than that still runs where a smaller reservation of spare planes fits
+ * (FP32 plans at N_x other than 128, 256 and 512 have one; for the others the two are the
+ * same): it then splits the bins fewer ways, so that the image differs in the order of
+ * FP32 sums (about 1e-7) and n_split and the offsets after accum are those of the smaller
+ * layout.  pam_workspace_layout_in reports the layout that a call uses in a workspace of
+ * ws_bytes bytes; where not even the smaller one fits it returns PAM_ERR_WORKSPACE, as the
+ * call would, and *layout is that smaller layout, its total the least that is accepted
+ * (ws_bytes = 0 asks for it).  Calls of the same frames in the same layout give the same
+ * bits. */
 pam_status_t pam_workspace_size(pam_plan_t p, int64_t n_frames, int32_t n_t, size_t* bytes);
 pam_status_t pam_workspace_layout(pam_plan_t p, int64_t n_frames, int32_t n_t,
                                   pam_workspace_layout_t* layout);
+pam_status_t pam_workspace_layout_in(pam_plan_t p, int64_t n_frames, int32_t n_t, size_t ws_bytes,
+                                     pam_workspace_layout_t* layout);
 
 /* Reconstruct n_frames frames (asynchronous on hip_stream; NULL = default stream).
  *   rf        device float32 [n_frames][L][n_t], time fastest               (in)
@@ -171,7 +182,8 @@ pam_status_t pam_workspace_layout(pam_plan_t p, int64_t n_frames, int32_t n_t,
  *   nncc      device float32 [n_frames][n_z][N_x], rho_n, or NULL           (out)
  *   rho_pairs device float32 [n_frames][n_pairs][n_z][N_x], NCC of each pair
  *             (12, 23, 31) before the eps floor, or NULL                    (out)
- *   workspace device scratch of at least pam_workspace_size bytes, 256-byte aligned
+ *   workspace device scratch of ws_bytes bytes, 256-byte aligned: pam_workspace_size bytes,
+ *             or less as pam_workspace_layout_in says
  * n_frames may be 0 (nothing is enqueued). */
 pam_status_t pam_as_tax(pam_plan_t p, const float* rf, int64_t n_frames, int32_t n_t,
                         float* image, float* nncc, float* rho_pairs,
@@ -216,9 +228,9 @@ pam_status_t pam_fd_tea_tax(pam_plan_t p, const float* rf, int64_t n_frames, int
  * and results as pam_as_tax; the intermediate results live in a device array of
  * PAM_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on until the
  * process ends.
- *   Errors: PAM_ERR_WORKSPACE when the call needs more scratch than
- *   PAM_NOALLOC_SCRATCH_BYTES (pam_workspace_size gives the need; split the frames
- *   into smaller calls); otherwise as pam_as_tax.
+ *   Errors: PAM_ERR_WORKSPACE when pam_workspace_layout_in for PAM_NOALLOC_SCRATCH_BYTES
+ *   says so (split the frames into smaller calls); otherwise as pam_as_tax.  The results are
+ *   those of pam_as_tax with a workspace of PAM_NOALLOC_SCRATCH_BYTES.
  *   Concurrency: every call on one GPU shares that GPU's scratch, which keeps the last
  *   call's contents; calls that overlap on one GPU (other streams, other threads) race
  *   and must be serialised by the caller.  No stage needs the scratch cleared: every
@@ -233,14 +245,15 @@ pam_status_t pam_as_tax_noalloc(pam_plan_t p, const float* rf, int64_t n_frames,
  * in all).  rf (device) holds the groups back to back, group g as
  * [n_frames][L][n_t] after the groups before it; image, nncc (and rho_pairs) hold the
  * frames in the same order.  Stages K1, K2 and K4 run per group.  On the factored fields
- * kernels (N_x = 256 or 512, and 128 with FP32 operands) the fields stage runs as one launch
+ * kernels (every N_x with FP32 operands, 256 and 512 with the others) the fields stage runs as one launch
  * over all groups (a grouped work list, one bin split for the call) when the library's cost
  * estimate of that launch is below the sum of the groups' own launches; otherwise, and on
  * the other kernels, it runs per group with each group's own split.  The workspace
  * (pam_workspace_size_grouped bytes, 256-byte aligned) holds the groups' workspaces back to
  * back, each laid out as pam_workspace_layout would for that group and split; it serves any
  * group list whose groups, position by position, have no more frames and no longer
- * records.  Results equal pam_as_tax on each group up to FP32 summation order (the bin split
+ * records.  With less than that every group takes the smaller reservation, if all of them
+ * then fit.  Results equal pam_as_tax on each group up to FP32 summation order (the bin split
  * depends on the frames of the call).  Errors as pam_as_tax; PAM_ERR_INVALID_ARG for a bad
  * group list. */
 typedef struct {

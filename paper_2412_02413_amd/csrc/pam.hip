@@ -260,7 +260,7 @@ std::vector<int32_t> select_bins(const pam_geometry_t* g) {
 struct LaunchShape {
   int n_dt, nw, xt, n_xg, n_split, bins_per_split;
   int ct;   // > 0: 16-depth kernels with ct 16-column tiles per consumer wave
-  int fw;   // < 0: the factored two-stage kernel (N = 256, 512)
+  int fw;   // < 0: a factored kernel (k3fft, k3ff), all columns in a workgroup
 };
 
 // Workgroup tiling of one frame: depth tiles x column groups, before any bin split.
@@ -446,6 +446,14 @@ pam_status_t layout(const pam_plan_s* p, int64_t F, int n_t, pam_workspace_layou
   L.n_acc = n_acc(p->n_sub, p->coherence);
   *out = L;
   return PAM_OK;
+}
+
+// The layout of a call in a workspace of ws_bytes bytes: the full reservation where it fits, else the smaller one
+// (PAM_ERR_WORKSPACE, *out still set to it, where that does not fit either).
+pam_status_t layout_in(const pam_plan_s* p, int64_t F, int n_t, size_t ws_bytes, pam_workspace_layout_t* out) {
+  pam_status_t st = layout(p, F, n_t, out);
+  if (st == PAM_OK && out->total > ws_bytes) st = layout(p, F, n_t, out, -1, false);
+  return st == PAM_OK && out->total > ws_bytes ? PAM_ERR_WORKSPACE : st;
 }
 
 // Where a K3 dispatch goes: a launch on stream st, or, with occ set, no launch but the
@@ -880,6 +888,12 @@ pam_status_t pam_workspace_layout(pam_plan_t p, int64_t n_frames, int32_t n_t, p
   return layout(p, n_frames, n_t, out);
 }
 
+pam_status_t pam_workspace_layout_in(pam_plan_t p, int64_t n_frames, int32_t n_t, size_t ws_bytes,
+                                     pam_workspace_layout_t* out) {
+  if (!p || !out || n_frames < 0) return PAM_ERR_INVALID_ARG;
+  return layout_in(p, n_frames, n_t, ws_bytes, out);
+}
+
 pam_status_t pam_workspace_size(pam_plan_t p, int64_t n_frames, int32_t n_t, size_t* bytes) {
   if (!bytes) return PAM_ERR_INVALID_ARG;
   pam_workspace_layout_t L;
@@ -957,7 +971,7 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
   int cap[pam::kMaxGroups];
   bool one_launch = false;
   pam_status_t st = grouped_layout(p, groups, n_groups, W, wbase, &total, cap, &one_launch);
-  if (st == PAM_OK && workspace && ws_bytes < total)        // the smaller reservation, where the plan has one
+  if (st == PAM_OK && workspace && ws_bytes < total)        // the smaller reservation (one group: as layout_in)
     st = grouped_layout(p, groups, n_groups, W, wbase, &total, cap, &one_launch, false);
   if (st != PAM_OK) return st;
   if (events && n_groups != 1) return PAM_ERR_INVALID_ARG;
@@ -1332,11 +1346,8 @@ pam_status_t pam_as_tax_noalloc(pam_plan_t p, const float* rf, int64_t n_frames,
                                 float* nncc, float* rho_pairs, void* hip_stream) {
   if (!p || n_frames < 0) return PAM_ERR_INVALID_ARG;
   pam_workspace_layout_t W;
-  pam_status_t st = layout(p, n_frames, n_t, &W);
+  pam_status_t st = layout_in(p, n_frames, n_t, (size_t)PAM_NOALLOC_SCRATCH_BYTES, &W);
   if (st != PAM_OK) return st;
-  if (W.total > (size_t)PAM_NOALLOC_SCRATCH_BYTES) st = layout(p, n_frames, n_t, &W, -1, false);
-  if (st != PAM_OK) return st;
-  if (W.total > (size_t)PAM_NOALLOC_SCRATCH_BYTES) return PAM_ERR_WORKSPACE;
   if (n_frames == 0) return PAM_OK;
   void* ws = nullptr;
   {

@@ -79,6 +79,8 @@ def _lib():
         lib.pam_workspace_size.restype = C.c_int
         lib.pam_workspace_layout.argtypes = [vp, i64, i32, C.POINTER(LayoutC)]
         lib.pam_workspace_layout.restype = C.c_int
+        lib.pam_workspace_layout_in.argtypes = [vp, i64, i32, sz, C.POINTER(LayoutC)]
+        lib.pam_workspace_layout_in.restype = C.c_int
         lib.pam_as_tax.argtypes = [vp, vp, i64, i32, vp, vp, vp, vp, sz, vp]
         lib.pam_as_tax.restype = C.c_int
         lib.pam_as_tax_events.argtypes = [vp, vp, i64, i32, vp, vp, vp, vp, sz, vp, C.POINTER(vp)]
@@ -275,6 +277,16 @@ def pam_workspace_layout(plan: Plan, n_frames: int, n_t: Optional[int] = None) -
     n_t = plan.info.n_samples if n_t is None else n_t
     _check(_lib().pam_workspace_layout(C.c_void_p(plan.handle), n_frames, n_t, C.byref(lay)),
            "pam_workspace_layout")
+    return lay
+
+
+def pam_workspace_layout_in(plan: Plan, n_frames: int, ws_bytes: int, n_t: Optional[int] = None) -> LayoutC:
+    """The layout a call uses in a workspace of ws_bytes bytes; if none fits, the smallest accepted
+    one (its total then exceeds ws_bytes, and the call would raise PAM_ERR_WORKSPACE)."""
+    lay = LayoutC()
+    n_t = plan.info.n_samples if n_t is None else n_t
+    st = _lib().pam_workspace_layout_in(C.c_void_p(plan.handle), n_frames, n_t, ws_bytes, C.byref(lay))
+    _check(PAM_OK if st == PAM_ERR_WORKSPACE else st, "pam_workspace_layout_in")
     return lay
 
 
