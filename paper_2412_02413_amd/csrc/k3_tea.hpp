@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea_few(TeaArgs a) {
     for (int s = 0; s < NSUB; ++s) accS[s] = fmaf(p[s].x, p[s].x, fmaf(p[s].y, p[s].y, accS[s]));
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-      const float2 v = p[c], w = p[NSUB == 3 ? (c + 1) % 3 : 1];
+      const float2 v = p[c], w = p[NSUB == 3 ? (c + 1) % 3 : NSUB - 1];
       accC[c] = fmaf(v.x, w.x, fmaf(v.y, w.y, accC[c]));
     }
   }

@@ -62,6 +62,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_kernel(ConvArgs a) {
   constexpr int NW = 9 * CO * 4;                 // 16-byte weight pieces per chunk
   constexpr int PIN = (NIN + 255) / 256;         // per thread
   constexpr int PW = (NW + 255) / 256;
+  constexpr int TAPS = RW * NO > 2 ? 3 : 9;      // unrolled together
   extern __shared__ __align__(16) bf16 lds_c[];
   bf16* xin = lds_c;                             // [PR][34][kConvPad]
   bf16* wts = lds_c + PR * 34 * kConvPad;        // [9][CO][kConvPad]
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_kernel(ConvArgs a) {
     if (it + 1 < n_items) fetch(it + 1, nch > 1);
     // taps unrolled so that a tap's operand reads run ahead of the products before it: all nine where the
     // accumulators leave room, three (a row) where nine spill (32 -> 32 channels of 8 x 512 x 256: 52 us against 49)
-#pragma unroll (RW * NO > 2 ? 3 : 9)
+#pragma unroll TAPS
     for (int t = 0; t < 9; ++t) {
       int dh = t / 3 - 1, dw = t % 3 - 1;
       if (a.flip) {
