@@ -615,6 +615,8 @@ __global__ __launch_bounds__(LOSS ? 1024 : 256) void head_kernel(const bf16* __r
         dz[2 * p] = (m - t) * wp;
         dz[2 * p + 1] = (e - ae) * wp;
       }
+    } else {
+      break;                                            // the grid covers every pixel
     }
   }
   if constexpr (LOSS) {
