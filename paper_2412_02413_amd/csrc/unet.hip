@@ -988,17 +988,20 @@ pam_status_t pam_nn_conv3x3(const void* x, int32_t ldx, int32_t batch, int32_t h
              w, k_in, ldy, n_out, relu, flip, accumulate, 0, w / 32, 0, 1};
   // 64 output channels x 8 rows per tile where the channels allow, else 32 x 16; runs of
   // up to 8 tiles per workgroup, as long as about 512 workgroups (two per CU, the LDS
-  // limit) remain.  A layer with less than two workgroups per CU that way is bound by the
-  // serial chain of its chunks, so it takes tiles of half the rows, and one with less than
-  // half a workgroup per CU 32 channels x 4 rows.  256 -> 256 channels of 32-pixel rows: 8 x 64
-  // rows 35 -> 34 us, 4 x 64 32 -> 25, 1 x 64 30 -> 19; 32 -> 32 of 512 x 256 11.5 -> 9.5; with 4-row
-  // tiles from 512 workgroups up (128 -> 128 of 8 x 128 x 64) 30 -> 37.  A pixel's sum keeps its order.
+  // limit) remain.  A layer with few workgroups that way is bound by the serial chain of
+  // its chunks, so it takes tiles of half the rows where these still are one round (512
+  // workgroups), and one with less than half a workgroup per CU 32 channels x 4 rows.
+  // 256 -> 256 channels of 32-pixel rows: 8 x 64 rows 35 -> 34 us, 4 x 64 32 -> 25, 1 x 64
+  // 30 -> 19; 32 -> 32 of 512 x 256 11.5 -> 9.5.  A second round costs more than it gives: over
+  // 250 drawn sizes half tiles are 1.05 to 1.6 times as fast up to 512 of them and 0.79 to
+  // 1.09 beyond (256 -> 128 of 4 x 59 x 224, 840 half tiles: 44 -> 52 us).  A pixel's sum
+  // keeps its order.
   const bool wide = n_out % 64 == 0;
   const auto tiles_of = [&](int rows) { return (int64_t)batch * ((h + rows - 1) / rows) * (w / 32); };
   int rows = wide ? 8 : 16, ch = wide ? 64 : 32;
   const int64_t full = tiles_of(rows) * (n_out / ch);
-  if (full < 512) rows /= 2;
   if (full < 128) rows = 4, ch = 32;
+  else if (tiles_of(rows / 2) * (n_out / ch) <= 512) rows /= 2;
   a.n_rt = (h + rows - 1) / rows;
   const int64_t tiles = tiles_of(rows);
   if (tiles > 0x7fffffffLL) return PAM_ERR_INVALID_ARG;
