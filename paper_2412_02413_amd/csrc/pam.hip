@@ -324,6 +324,42 @@ int64_t k3_spare_planes(const pam_plan_s* p, bool full = true) {
   return full ? std::max(spare, small) : small;
 }
 
+// Estimated time of a K3 launch under the bins-per-workgroup cap b, in bin-times of a workgroup that has its CU to
+// itself (measured 1.8, 2.8 and 4.0 us with one, two and three sub-apertures at 256 columns in FP32).  A CU's second and
+// third workgroup slow each other down: a bin then takes 1.3 and 1.7 times as long (16-bit operands 1.65 and more), so
+// workgroups beyond one per CU give much less than those up to it.  Four bin-times go to a launch's start and its end,
+// two and a half to each further round, and every split adds a partial-sum plane per frame that K3 writes and K4 reads
+// (2.5 TB/s for both).  Several groups of unequal workgroups: the work over the slots plus 0.7 of a longest workgroup.
+double k3_time(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, int b) {
+  const LaunchShape t = k3_tiles(p);
+  const double tiles = (double)t.n_dt * t.n_xg, cus = std::max(1, p->n_cus);
+  const int occ = std::max(1, p->k3_slots / std::max(1, p->n_cus));
+  const double crowd = is_split(p->precision) ? 0.65 : 0.35;
+  const auto bin_time = [&](int m) { return m == 0 ? 0.0 : 1.0 + crowd * (m - 1); };
+  const double us = p->n_sub == 3 ? 4.0 : (p->n_sub == 2 ? 2.8 : 1.8);
+  const double plane = (double)n_acc(p->n_sub, p->coherence) * p->n_z * p->N * 4.0 / 2.5e12 * 1e6 / us;
+  double wg = 0, work = 0, planes = 0;
+  int job = 0, live = 0;
+  for (int g = 0; g < n; ++g) {
+    if (F[g] == 0 || n_sel[g] == 0) continue;
+    const int split = (n_sel[g] + b - 1) / b, bins = (n_sel[g] + split - 1) / split;
+    ++live;
+    wg += F[g] * tiles * split;
+    work += F[g] * tiles * split * bins;
+    planes += (double)F[g] * split;
+    job = std::max(job, bins);
+  }
+  double k3 = 4.0;
+  if (live > 1) {
+    k3 += (work + 2.5 * wg) * bin_time(occ) / (occ * cus) + 0.7 * job;
+  } else {
+    const double per_cu = std::ceil(wg / cus), rounds = std::ceil(per_cu / occ);
+    const double full = std::floor(per_cu / occ);
+    k3 += 2.5 * (rounds - 1) + job * (full * bin_time(occ) + bin_time((int)(per_cu - full * occ)));
+  }
+  return k3 + plane * planes;
+}
+
 // The bin split of a K3 launch over n groups of frames (F[g] frames of n_sel[g] bins).
 // A frame is tiles = n_dt n_xg workgroups; splitting its bins s ways makes s workgroups of
 // ceil(n_sel / s) bins each, whose partial sums K4 adds.  The device holds p->k3_slots
@@ -332,14 +368,9 @@ int64_t k3_spare_planes(const pam_plan_s* p, bool full = true) {
 // start and its partial-sum write, and every split beyond the first costs K4 one more
 // partial-sum plane per frame (n_acc pix floats, read at about 4 TB/s against about 5 us
 // per bin).  Returns the bins-per-workgroup cap b (every group splits into ceil(n_sel / b)
-// parts) that minimises the estimate, the largest such b on ties, at least 4 bins (or the
-// widest band when narrower), among the caps whose splits fit the spare planes.  Against at
-// least 8 bins one frame of 151 x 128 pixels and 205 bins takes 45.7 us instead of 53.1, one
-// of 93 x 384 65.9 instead of 82.1; 2 bins measure the same as 4 there and worse with one or
-// two sub-apertures (27.5 against 26.6 us).  Plans with coherence keep 8: their sums become
-// BF16 features, where another order of the FP32 sums moves the network's output.
-int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr,
-               bool full = true) {
+// parts) that minimises the estimate, the largest such b on ties, at least `floor` bins (or
+// the widest band when narrower), among the caps whose splits fit the spare planes.
+int k3_cap_from(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, int floor, double* cost_out, bool full) {
   const LaunchShape t = k3_tiles(p);
   const int64_t tiles = (int64_t)t.n_dt * t.n_xg;
   const int64_t spare = k3_spare_planes(p, full);
@@ -355,7 +386,7 @@ int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, d
   // top of each such piece: for every group g and split count s, the largest cap that splits g s ways
   // (n_g for s = 1, ceil(n_g / (s - 1)) - 1 after), in decreasing order (a merge over the groups' sequences,
   // no storage).  This equals trying every cap.
-  const int min_b = std::min(p->coherence ? 8 : 4, max_n);
+  const int min_b = std::min(floor, max_n);
   auto top = [&](int g, int s) { return s == 1 ? n_sel[g] : (n_sel[g] + s - 2) / (s - 1) - 1; };
   int next_s[pam::kMaxGroups];
   int live = 0;
@@ -399,6 +430,20 @@ int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, d
   }
   if (cost_out) *cost_out = best;
   return best_b;
+}
+
+// The cap of a launch: the estimate's with at least 8 bins a workgroup, or with at least 4 where k3_time finds that
+// faster by 7 % (its spread).  Down to 4 gains where CUs stand empty (one frame of 151 x 128 pixels and 205 bins 53.1 ->
+// 45.7 us, one of 93 x 384 82.1 -> 65.9; over 300 drawn calls 1.18 on average where the two differ) and loses where each CU
+// has a workgroup already (19 frames of 166 x 128 and 13 bins with two sub-apertures: 39.0 us in two splits, 44.7 in
+// four); 2 bins measure the same as 4 or worse.  Plans with coherence keep 8: their sums become BF16 features, where
+// another order of the FP32 sums moves the network's output.  *cost_out: the estimate at 8.
+int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr,
+               bool full = true) {
+  const int b8 = k3_cap_from(p, F, n_sel, n, 8, cost_out, full);
+  if (p->coherence) return b8;
+  const int b4 = k3_cap_from(p, F, n_sel, n, 4, nullptr, full);
+  return b4 < b8 && k3_time(p, F, n_sel, n, b4) < 0.93 * k3_time(p, F, n_sel, n, b8) ? b4 : b8;
 }
 
 // The launch shape of one group: its tiling, and its bins split under the cap b.
