@@ -28,3 +28,34 @@ def test_bin_split(n_x, n_z, n_sub, n_samples, hi, frames, splits, precision):
         assert n == splits
     finally:
         pam.pam_destroy(plan)
+
+
+@pytest.mark.parametrize("n_x,n_z,n_sub,n_samples,hi,groups,one", [
+    (256, 219, 3, 256, 9e6, [(64, 1), (32, 13)], True),              # 92 us in one launch, 105 apart
+    (96, 502, 2, 256, 9e6, [(32, 10), (128, 6), (32, 3)], True),     # 117, 130
+    (384, 17, 2, 8192, 5e6, [(8192, 23), (1024, 1)], False),         # 1,446, 1,257
+])
+def test_grouped_launch(n_x, n_z, n_sub, n_samples, hi, groups, one):
+    """The schedule taken, and every frame equal to the per-length call up to the order of FP32 sums (1e-5 of the
+    image, as for the grouped call everywhere)."""
+    import torch
+    from paper_2412_02413_amd import pam
+    g = geometry(n_x, n_z, n_sub, n_samples, hi)
+    plan = pam.pam_plan(g, 0, "fp32")
+    try:
+        assert pam.debug_grouped_one_launch(plan, groups) == one
+        F = sum(f for _, f in groups)
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        parts = [torch.randn((f, 64, n), generator=gen, device="cuda") for n, f in groups]
+        img = torch.empty((F, n_z, n_x), device="cuda")
+        pam.pam_as_tax_grouped(plan, torch.cat([p.view(-1) for p in parts]), groups, img, None, None,
+                               pam.alloc_workspace_grouped(plan, groups))
+        at = 0
+        for p in parts:
+            alone = pam.reconstruct(plan, p)["image"]
+            got = img[at: at + len(p)]
+            e = ((got - alone).double().norm(dim=(1, 2)) / alone.double().norm(dim=(1, 2))).max().item()
+            assert e <= 1e-5, e
+            at += len(p)
+    finally:
+        pam.pam_destroy(plan)
