@@ -1227,9 +1227,11 @@ pam_status_t run_groups(pam_plan_t p, const float* rf, const pam_group_t* groups
       else if (p->n_sub == 2) hipLaunchKernelGGL((pam::k4_weight<2, SG>), grid, block, 0, stream, a);
       else hipLaunchKernelGGL((pam::k4_weight<1, SG>), grid, block, 0, stream, a);
     };
-    // four threads a pixel once each has a split to add (16 splits of 131,072 pixels: 31 -> 10.5 us); with one or
-    // two splits the loads of one thread are in flight together already and more threads only add the LDS step
-    if (W[g].n_split >= 4) weight(std::integral_constant<int, 4>());
+    // Four threads a pixel where a pixel has many splits to add and the pixels alone leave CUs with little to do: up to 256
+    // workgroups of 256 pixels (512 with one sub-aperture) and from 16 splits.  This stage, with three sub-apertures: 76
+    // workgroups of 52 splits 14.0 us with one thread a pixel and 12.0 with four, 152 of 32 12.2 / 11.7, 256 of 16 11.0 /
+    // 11.2, 512 of 16 14.2 / 14.6, 1,216 of 4 12.2 / 14.4; with one sub-aperture 512 of 23 10.2 / 9.8, 2,432 of 4 11.2 / 16.7.
+    if (W[g].n_split >= 16 && (long long)n_blk * q.F <= (p->n_sub == 1 ? 512 : 256)) weight(std::integral_constant<int, 4>());
     else weight(std::integral_constant<int, 1>());
     if (hipGetLastError() != hipSuccess) return PAM_ERR_DEVICE;
     hipLaunchKernelGGL(pam::k4_image, dim3(n_blk, q.F), dim3(256), 0, stream, a);
