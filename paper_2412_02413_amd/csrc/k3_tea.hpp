@@ -27,9 +27,14 @@
 // ~2e-5 cycle at 8 MHz.
 //
 // One frame of 512 x 256 pixels, 128 elements and 768 bins: 7.3 ms with one thread a pixel making every
-// (pixel, element, bin) phasor, 1.58 ms here (66 TFLOP/s of the 78.6 of unpacked vector FMAs; spectra and sub-aperture
-// sets through vector loads instead of scalar ones: 1.9 ms).
+// (pixel, element, bin) phasor, 1.54 ms here (67 TFLOP/s of the 78.6 of unpacked vector FMAs; spectra and sub-aperture
+// sets through vector loads instead of scalar ones: 1.9 ms).  A launch that leaves SIMDs with one wave or none is bound by
+// latency instead: 4 frames of 34 x 288 pixels, 190 elements and 13 bins took 182 us (one thread a pixel 148) with every
+// unit waiting for its own spectra, code and phasors and 118 with the first two asked for ahead; one of 5 x 224
+// zero-stuffed 16.4 -> 12.0 with fewer rows a wave.
 #pragma once
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace pam {
@@ -61,6 +66,9 @@ inline void tea_shape(TeaArgs& a) {
   a.chunks = (q + 63) / 64;
   a.rows = 64 / a.Q;
   a.PL = a.Q + 2 * ((a.L + 7) / 8);
+  // a launch of less than a wave per SIMD (1,024) packs fewer rows into a wave: each row's table is that wave's own work
+  const long long row_waves = (long long)a.n_z * a.step * a.chunks * a.F * a.n_split;
+  a.rows = (int)std::max(1ll, std::min((long long)a.rows, row_waves / 1024));
   const long long waves = ((long long)a.n_z * a.step + a.rows - 1) / a.rows * a.chunks;
   a.n_wg = (int)((waves + TEA_WAVES - 1) / TEA_WAVES);
 }
@@ -123,6 +131,14 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
   double* u = lds_tea + (size_t)w * a.rows * entries;
   float2* E = reinterpret_cast<float2*>(lds_tea + (size_t)TEA_WAVES * a.rows * entries) + (size_t)w * a.rows * entries;
 
+  // The scalar loads of a bin's spectra are a serial chain of 64-byte lines that this XCD's L2 has not seen; one vector
+  // load a bin, a lane a line, brings the next bin's lines in (up to 512 elements) while this one's products run.
+  const auto touch = [&](int b) {
+    const size_t line = ((size_t)f * a.n_sel + b) * a.L + min(8 * lane, a.L - 1);
+    return b_begin < b_end ? a.spectra[line].x : 0.f;
+  };
+  const float first = touch(b_begin);
+
   // plane p, position n of a row: D = 4 n + p - (8 units - 1) + first pixel of the chunk
   for (int s = lane; s < a.rows * entries; s += 64) {
     const int row = row0 + s / entries, e = s % entries;
@@ -132,6 +148,7 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
     u[s] = sqrt(x * x + z * z) * a.cyc;
   }
 
+  asm volatile("" ::"v"(first));
   const int slot = lane / a.Q;                                      // lanes past the wave's rows repeat row 0
   const bool lane_live = slot < a.rows && row0 + slot < n_rows;
   const int q = lane % a.Q;
@@ -149,6 +166,7 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
 
   for (int b = b_begin; b < b_end; ++b) {
     const double k = (double)a.ksel[b];
+    const float ahead = touch(min(b + 1, b_end - 1));
     for (int s = lane; s < a.rows * entries; s += 64) {
       const double ph = k * u[s];
       const float r = (float)(ph - rint(ph));
@@ -163,8 +181,10 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
       for (int i = 0; i < TEA_PX; ++i) p[s][i] = make_float2(0.f, 0.f);
     float x[16], xn[16];                                            // this unit's spectra, the next one's
     tea_load(x, X);
-    auto unit = [&](int un, auto&& mac) {                           // mac(j, x_j, lo, hi) for the unit's elements
-      tea_load(xn, X + 16 * min(un + 1, units - 1));                // in flight during this unit's products
+    int code = codes[0], code_n = 0;                                // this unit's code, the next one's
+    // mac(j, x_j, lo, hi) for the unit's elements.  The next unit's spectra and code are asked for once this unit's
+    // phasors are here: scalar and LDS loads share a counter, so asked for before them, every unit would wait for both.
+    auto unit = [&](int un, auto&& mac) {
       const float2* Ep = Eq + 2 * (units - 1 - un);
       float2 e0[4], e1[4], e2[4];                                   // positions q + B, q + B + 1, q + B + 2
 #pragma unroll
@@ -173,15 +193,19 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
         e1[c] = Ep[c * a.PL + 1];
         e2[c] = c < 3 ? Ep[c * a.PL + 2] : e1[c];
       }
+      mac(0, 0, make_float2(x[0], x[1]), e1, e2);
+      __builtin_amdgcn_sched_barrier(0);
+      tea_load(xn, X + 16 * min(un + 1, units - 1));
+      code_n = codes[min(un + 1, units - 1)];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) mac(j, j, make_float2(x[2 * j], x[2 * j + 1]), e1, e2);
+      for (int j = 1; j < 4; ++j) mac(j, j, make_float2(x[2 * j], x[2 * j + 1]), e1, e2);
 #pragma unroll
       for (int j = 0; j < 4; ++j) mac(4 + j, j, make_float2(x[8 + 2 * j], x[8 + 2 * j + 1]), e0, e1);
 #pragma unroll
       for (int j = 0; j < 16; ++j) x[j] = xn[j];
     };
     for (int un = 0; un < units;) {
-      const int code = codes[un];
       if (MIXED && (code >> 24) == kTeaMixed) {
         unit(un, [&](int j8, int j, float2 xj, const float2 (&lo)[4], const float2 (&hi)[4]) {
 #pragma unroll
@@ -189,6 +213,7 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
             if (code >> (3 * j8 + s) & 1) tea_mac(p[s], xj, j, lo, hi);
         });
         ++un;
+        code = code_n;
         continue;
       }
       bool done = false;
@@ -199,15 +224,18 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
             unit(un, [&](int, int j, float2 xj, const float2 (&lo)[4], const float2 (&hi)[4]) {
               tea_mac(p[s], xj, j, lo, hi);
             });
-          } while (++un < units && codes[un] >> 24 == s);
+            code = code_n;
+          } while (++un < units && code >> 24 == s);
           done = true;
         }
       if (!done) {                                                  // no sub-aperture holds any of the eight
         ++un;
         tea_load(x, X + 16 * min(un, units - 1));
+        code = codes[min(un, units - 1)];
       }
     }
     __builtin_amdgcn_wave_barrier();                                // the table is free for the next bin
+    asm volatile("" ::"v"(ahead));                                  // the touched lines are here by now
 #pragma unroll
     for (int i = 0; i < TEA_PX; ++i) {
 #pragma unroll

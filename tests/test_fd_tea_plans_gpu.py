@@ -74,3 +74,16 @@ def test_few_elements(env, L, n_x, lateral, n_sub, kw):
     g = synth.Geometry(n_elements=L, pitch_m=0.3 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=128, bands_hz=[(2e6, 6e6)],
                        depths_m=(12 + 0.7 * np.arange(11)) * MM, n_x=n_x, n_sub=n_sub, lateral=lateral).replace(**kw)
     check_fd_tea(env, g, 2, L + n_x)
+
+
+@pytest.mark.parametrize("L,n_x,lateral,n_z,kw", [
+    (13, 32, "pad", 2101, {"pattern_m": 3}),       # several rows a wave, a ragged last wave; mixed units
+    (9, 288, "stuff", 130, {"pattern_m": 1}),      # 32 residues a depth
+    (48, 96, "stuff", 601, {}),                    # rows of 12 lanes
+    (190, 288, "pad", 34, {"pattern_m": 3}),       # one row a wave, two waves a row, 24 units
+])
+def test_rows_per_wave(env, L, n_x, lateral, n_z, kw):
+    """Launches of more and of less than a wave per SIMD, which pack several rows or one into a wave."""
+    g = synth.Geometry(n_elements=L, pitch_m=0.1 * MM, fs_hz=20e6, c_mps=1540.0, n_samples=64, bands_hz=[(2e6, 5e6)],
+                       depths_m=(12 + 8.0 / n_z * np.arange(n_z)) * MM, n_x=n_x, n_sub=3, lateral=lateral).replace(**kw)
+    check_fd_tea(env, g, 2, L)
