@@ -404,8 +404,10 @@ __device__ __forceinline__ float partner_column(float v) {
 // EARLY: with one sub-aperture (up to 256 columns) the next bin's inputs are stored and the bin's barrier passed before
 // stage 3, which ends their registers there; with three it measured 1 % slower at 512 columns.
 // LEAN (with the pair sums): EARLY and the twiddles read where they are used, 164 registers instead of 194, so that three
-// workgroups fit a CU.  64 frames of the benchmark array 8.67 -> 7.76 ms, 24 frames in two bin splits 3.35 -> 3.05; but
-// 16 frames, two workgroups per CU, 2.27 -> 2.45, so launches of at most two per CU keep the other form (2.28).
+// workgroups fit a CU.  64 frames of the benchmark array 8.67 -> 7.76 ms, 24 frames in two bin splits 3.35 -> 3.05, and
+// over workgroups per CU 1.17 to 1.21 times as fast at three and 1.09 to 1.14 beyond four; but up to two it is 0.90 to
+// 0.96 (16 frames 2.28 ms against 2.45), and at four, which it runs as three and one, 1.03 with 8 bins a workgroup, 0.99
+// with 24 and 0.95 with 55, so those launches keep the other form.
 template <int NSUB, bool COH = false, int NN = 256, bool LEAN = false>
 __global__ __launch_bounds__(256, 2) void k3fft(K3Args a0, K3Groups grp) {
   static_assert(!COH || (NSUB == 1 && NN == 256), "pair cross-spectra come with the full-aperture sums at N = 256");

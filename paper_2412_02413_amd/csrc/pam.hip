@@ -630,8 +630,8 @@ hipError_t launch_k3(int precision, int n_sub, const LaunchShape& s, const pam::
       case PAM_PREC_BF16: return launch_big_lds(k3ff<__bf16, 1, 1, true>, kFfWaves, lds, a, grp, blocks, st);
       case PAM_PREC_FP16: return launch_big_lds(k3ff<_Float16, 1, 1, true>, kFfWaves, lds, a, grp, blocks, st);
       default:
-        // more workgroups than two per CU: the form of which three fit (both measured at k3fft)
-        if (blocks > 2 * st.n_cus)
+        // the form of which three workgroups fit a CU where that saves a round: at three per CU and beyond four (at k3fft)
+        if (const int per_cu = st.n_cus > 0 ? (blocks + st.n_cus - 1) / st.n_cus : 0; per_cu == 3 || per_cu > 4)
           return launch_big_lds(k3fft<1, true, 256, true>, kFtWaves, k3fft_lds<1, 256, true>(), a, grp, blocks, st);
         return launch_big_lds(k3fft<1, true>, kFtWaves, k3fft_lds<1, 256, true>(), a, grp, blocks, st);
     }
