@@ -368,25 +368,26 @@ double k3_time(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, i
 // start and its partial-sum write, and every split beyond the first costs K4 one more
 // partial-sum plane per frame (n_acc pix floats, read at about 4 TB/s against about 5 us
 // per bin).  Returns the bins-per-workgroup cap b (every group splits into ceil(n_sel / b)
-// parts) that minimises the estimate, the largest such b on ties, at least `floor` bins (or
-// the widest band when narrower), among the caps whose splits fit the spare planes.
-int k3_cap_from(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, int floor, double* cost_out, bool full) {
+// parts) that minimises the estimate, the largest such b on ties, among the caps whose
+// splits fit the spare planes: at least 8 bins in *cap8, with its cost, and at least 4 in
+// *cap4 (or the widest band when narrower).
+void k3_caps(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, bool full, int* cap8, double* cost8,
+             int* cap4) {
   const LaunchShape t = k3_tiles(p);
   const int64_t tiles = (int64_t)t.n_dt * t.n_xg;
   const int64_t spare = k3_spare_planes(p, full);
   int max_n = 0;
   for (int g = 0; g < n; ++g) max_n = std::max(max_n, n_sel[g]);
-  if (max_n == 0) {
-    if (cost_out) *cost_out = 0;
-    return 1;
-  }
+  *cap8 = *cap4 = std::max(1, max_n);
+  *cost8 = 0;
+  if (max_n == 0) return;
   const double slots = std::max(1, p->k3_slots);
   const double plane_cost = (double)n_acc(p->n_sub, p->coherence) * p->n_z * p->N * 4.0 / 4e12 / 5e-6;
   // The estimate is constant between the caps where some group's split count changes, so it is evaluated at the
   // top of each such piece: for every group g and split count s, the largest cap that splits g s ways
   // (n_g for s = 1, ceil(n_g / (s - 1)) - 1 after), in decreasing order (a merge over the groups' sequences,
   // no storage).  This equals trying every cap.
-  const int min_b = std::min(floor, max_n);
+  const int min8 = std::min(8, max_n), min4 = std::min(4, max_n);
   auto top = [&](int g, int s) { return s == 1 ? n_sel[g] : (n_sel[g] + s - 2) / (s - 1) - 1; };
   int next_s[pam::kMaxGroups];
   int live = 0;
@@ -395,13 +396,12 @@ int k3_cap_from(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, 
     live += F[g] > 0 && n_sel[g] > 0;
   }
   double best = 0;
-  int best_b = max_n;
   for (bool first = true;; first = false) {
     int b = -1;
     for (int g = 0; g < n; ++g)
       if (F[g] > 0 && n_sel[g] > 0) b = std::max(b, top(g, next_s[g]));
     if (first) b = max_n;
-    if (b < min_b) break;
+    if (b < min4) break;
     for (int g = 0; g < n; ++g)      // step every group past this cap
       if (F[g] > 0 && n_sel[g] > 0)
         while (top(g, next_s[g]) >= b) ++next_s[g];
@@ -425,11 +425,13 @@ int k3_cap_from(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, 
     const double cost = live > 1 ? work / slots + (job + 2.0) + k4 : std::ceil((double)n_wg / slots) * (job + 2.0) + k4;
     if (b == max_n || cost < best - 1e-9) {
       best = cost;
-      best_b = b;
+      *cap4 = b;
+      if (b >= min8) {
+        *cap8 = b;
+        *cost8 = cost;
+      }
     }
   }
-  if (cost_out) *cost_out = best;
-  return best_b;
 }
 
 // The cap of a launch: the estimate's with at least 8 bins a workgroup, or with at least 4 where k3_time finds that
@@ -440,10 +442,12 @@ int k3_cap_from(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, 
 // another order of the FP32 sums moves the network's output.  *cost_out: the estimate at 8.
 int k3_bin_cap(const pam_plan_s* p, const int64_t* F, const int* n_sel, int n, double* cost_out = nullptr,
                bool full = true) {
-  const int b8 = k3_cap_from(p, F, n_sel, n, 8, cost_out, full);
-  if (p->coherence) return b8;
-  const int b4 = k3_cap_from(p, F, n_sel, n, 4, nullptr, full);
-  return b4 < b8 && k3_time(p, F, n_sel, n, b4) < 0.93 * k3_time(p, F, n_sel, n, b8) ? b4 : b8;
+  int b8, b4;
+  double cost;
+  k3_caps(p, F, n_sel, n, full, &b8, &cost, &b4);
+  if (cost_out) *cost_out = cost;
+  if (b4 >= b8 || p->coherence) return b8;
+  return k3_time(p, F, n_sel, n, b4) < 0.93 * k3_time(p, F, n_sel, n, b8) ? b4 : b8;
 }
 
 // The launch shape of one group: its tiling, and its bins split under the cap b.
