@@ -34,6 +34,7 @@
 // zero-stuffed 16.4 -> 12.0 with fewer rows a wave.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -266,12 +267,13 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
 // Few elements: one thread a pixel makes its own phasors, with the delays in registers.  A row's table holds 4 PL phasors
 // however few pixels and elements the row has, so below some number of elements it costs more than it saves: of
 // 4 frames of 151 x 512 pixels and 205 bins, one element zero-stuffed takes 674 us with the table (12 phasors for each
-// one-pixel row) and 79 here, two 376 and 112, four 231 and 175, eight 232 and 313; padded (rows of 512 pixels in two
-// tables of 264) two take 129 and 110, three 134 and 142.  At 32 to 512 columns the two meet where a depth's pixels
-// times elements are about 2.8 of its table phasors, which tea_few takes as the line; at most six elements get there.
-constexpr int kTeaFew = 6;
+// one-pixel row) and 79 here, two 376 and 112, four 231 and 175; 3 frames of 317 x 384, 205 bins and six elements
+// zero-stuffed 303 and 184.  Timed both ways over 176 drawn calls of up to eight elements, this form is 1.05 to 1.65
+// times as fast where a depth's pixels times elements are at most 3.1 of its table phasors and 0.6 to 1.1 beyond 3.3
+// (calls above 30 us), so the line lies at 3.2; seven elements get there at most.
+constexpr int kTeaFew = 7;
 inline bool tea_few(const TeaArgs& a) {              // (a's shape set)
-  return a.L <= kTeaFew && 5ll * a.L * a.N <= 14ll * a.step * a.chunks * 4 * a.PL;
+  return a.L <= kTeaFew && 5ll * a.L * a.N <= 16ll * a.step * a.chunks * 4 * a.PL;
 }
 template <int NSUB>
 __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea_few(TeaArgs a) {
@@ -296,31 +298,51 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea_few(TeaArgs a) {
   for (int s = 0; s < NSUB; ++s) accS[s] = 0.f;
 #pragma unroll
   for (int c = 0; c < (NP > 0 ? NP : 1); ++c) accC[c] = 0.f;
-  for (int b = b_begin; b < b_end; ++b) {
-    const double k = (double)a.ksel[b];
-    const scalar_float* X = (const scalar_float*)(a.spectra + ((size_t)f * a.n_sel + b) * a.L);
-    float2 p[NSUB];
+  // four bins at a time, so that their spectra are asked for together and their phasors overlap; the rest one by one
+  const auto bins = [&](auto count, int b0) {
+    constexpr int BC = decltype(count)::value;
+    double k[BC];
+    const scalar_float* X[BC];
+    float2 p[NSUB][BC];
 #pragma unroll
-    for (int s = 0; s < NSUB; ++s) p[s] = make_float2(0.f, 0.f);
+    for (int c = 0; c < BC; ++c) {
+      k[c] = (double)((const scalar_int*)a.ksel)[b0 + c];
+      X[c] = (const scalar_float*)(a.spectra + ((size_t)f * a.n_sel + b0 + c) * a.L);
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) p[s][c] = make_float2(0.f, 0.f);
+    }
 #pragma unroll
     for (int l = 0; l < kTeaFew; ++l) {
       if (l >= a.L) break;
-      const double ph = k * u[l];
-      const float r = (float)(ph - rint(ph));
-      const float2 v = cmul(make_float2(X[2 * l], X[2 * l + 1]),
-                            make_float2(__builtin_amdgcn_cosf(r), __builtin_amdgcn_sinf(r)));
+      float2 v[BC];
+#pragma unroll
+      for (int c = 0; c < BC; ++c) v[c] = make_float2(X[c][2 * l], X[c][2 * l + 1]);
+#pragma unroll
+      for (int c = 0; c < BC; ++c) {
+        const double ph = k[c] * u[l];
+        const float r = (float)(ph - rint(ph));
+        v[c] = cmul(v[c], make_float2(__builtin_amdgcn_cosf(r), __builtin_amdgcn_sinf(r)));
+      }
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
-        if (code >> (3 * l + s) & 1) p[s] = cadd(p[s], v);
+        if (code >> (3 * l + s) & 1)
+#pragma unroll
+          for (int c = 0; c < BC; ++c) p[s][c] = cadd(p[s][c], v[c]);
     }
 #pragma unroll
-    for (int s = 0; s < NSUB; ++s) accS[s] = fmaf(p[s].x, p[s].x, fmaf(p[s].y, p[s].y, accS[s]));
+    for (int c = 0; c < BC; ++c) {
 #pragma unroll
-    for (int c = 0; c < NP; ++c) {
-      const float2 v = p[c], w = p[NSUB == 3 ? (c + 1) % 3 : NSUB - 1];
-      accC[c] = fmaf(v.x, w.x, fmaf(v.y, w.y, accC[c]));
+      for (int s = 0; s < NSUB; ++s) accS[s] = fmaf(p[s][c].x, p[s][c].x, fmaf(p[s][c].y, p[s][c].y, accS[s]));
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const float2 v = p[q][c], w = p[NSUB == 3 ? (q + 1) % 3 : NSUB - 1][c];
+        accC[q] = fmaf(v.x, w.x, fmaf(v.y, w.y, accC[q]));
+      }
     }
-  }
+  };
+  int b = b_begin;
+  for (; b + 4 <= b_end; b += 4) bins(std::integral_constant<int, 4>(), b);
+  for (; b < b_end; ++b) bins(std::integral_constant<int, 1>(), b);
   if (pix >= n_pix) return;
   float* dst = a.accum + ((size_t)sp * a.F + f) * a.n_acc * n_pix + pix;
 #pragma unroll

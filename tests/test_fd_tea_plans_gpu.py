@@ -64,9 +64,9 @@ def test_plan_with_pair_sums(env, frames, bins_hi):
     (2, 512, "pad", 3, {"pattern_m": 1}),
     (4, 64, "stuff", 3, {"apod": np.uint8([[1, 1, 0, 0], [0, 1, 1, 0], [0, 1, 0, 1]])}),   # in several and in none
     (5, 288, "pad", 3, {"pattern_m": 2}),
-    (6, 480, "stuff", 2, {"pattern_m": 2}),                   # ... to the most it takes
-    (3, 512, "pad", 3, {"pattern_m": 1}),                     # the table's first
-    (7, 224, "stuff", 3, {"pattern_m": 2}),
+    (3, 512, "pad", 3, {"pattern_m": 1}),
+    (7, 224, "stuff", 3, {"pattern_m": 2}),                   # ... to the most it takes
+    (4, 448, "pad", 3, {"pattern_m": 1}),                     # the table's first
     (8, 32, "stuff", 3, {"pattern_m": 2}),
 ])
 def test_few_elements(env, L, n_x, lateral, n_sub, kw):
