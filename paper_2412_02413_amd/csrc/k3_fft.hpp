@@ -197,9 +197,6 @@ __device__ __forceinline__ void idft16(float2 (&v)[16], In&& in, Out&& out) {
   out(3);
 }
 
-// Two workgroups per CU (at most 256 VGPRs a lane).  At N = 512 with three sub-apertures
-// this spills a few values per bin to scratch, which measures faster (about 1.4x) than one
-// workgroup per CU without spills.
 // An LDS address the compiler cannot see through: accesses at constant offsets from it keep this base, so that pairs of
 // 8-byte accesses merge into one instruction (their offsets are 8 bits wide; from a shared base they do not fit).
 typedef float f2v __attribute__((ext_vector_type(2)));
@@ -223,7 +220,7 @@ __device__ __forceinline__ lds_f2* lds_base(float2* p) {
 //   a = u_n2 +- (c_{8+n2} / c_n2) u_{8+n2}, b = u_{4+n2} +- (c_{12+n2} / c_{4+n2}) u_{12+n2},
 //   T = a +- (c_{4+n2} / c_n2) (i) b,
 // and s_n2 multiplies the second stage's constant twiddles.  144 + 30 operations at 16 points instead of 144 + 64.
-// The constants depend on the lane's row only: float4s k at c[16 k] (ft_constants on the host).  A cosine of zero (n x1 a
+// The constants depend on the lane's row only: float4s k at c[16 k] (ft_table on the host).  A cosine of zero (n x1 a
 // quarter turn of 16 K: (8, 8) at K = 16, (4, 8) at K = 8) is stored as 2^-30, its tangent as 2^30: the product is exact.
 __device__ __forceinline__ void bfly_scaled(float2& x0, float2& x1, float2& x2, float2& x3, float al, float be, float ga) {
   const float2 a0 = make_float2(fmaf(al, x2.x, x0.x), fmaf(al, x2.y, x0.y));
@@ -391,7 +388,7 @@ __device__ __forceinline__ float partner_column(float v) {
 }
 
 // Bound: the vector ALUs' issue (about 1,470 instructions per wave and bin at N = 256 and three sub-apertures), as long
-// as the LDS instructions keep out of each other's way.  A wave issues 82 of those a bin, and in bursts (sixteen row
+// as the LDS instructions keep out of each other's way.  A wave issues 89 of those a bin, and in bursts (sixteen row
 // writes, eight row reads, eight coefficient reads in a row) they stall both waves of a SIMD in the LDS queue, so they
 // are spread over the arithmetic, held in place by scheduling barriers: coefficients in two halves, the previous
 // sub-aperture's row reads between the columns of stage 1, row writes after each column of its second stage, and the
@@ -400,6 +397,9 @@ __device__ __forceinline__ float partner_column(float v) {
 // One frame of 1,024 x 512 pixels and 3,072 bins: 6.37 -> 5.55 ms; 4 of 301 x 192 and 691: 0.578 -> 0.535.
 // The mirrored propagator values through LDS instead of two DPP moves and a select (42 vector instructions fewer)
 // measured the same at N = 256 and 6 % slower at 512.
+//
+// Two workgroups per CU (at most 256 VGPRs a lane).  At N = 512 with three sub-apertures this spills a few values per bin
+// to scratch, which measures faster (about 1.4x) than one workgroup per CU without spills.
 //
 // EARLY: with one sub-aperture (up to 256 columns) the next bin's inputs are stored and the bin's barrier passed before
 // stage 3, which ends their registers there; with three it measured 1 % slower at 512 columns.

@@ -991,8 +991,9 @@ pam_status_t pam_nn_conv3x3(const void* x, int32_t ldx, int32_t batch, int32_t h
   // limit) remain.  A layer with few workgroups that way is bound by the serial chain of
   // its chunks, so it takes tiles of half the rows where these still are one round (512
   // workgroups), and one with less than half a workgroup per CU 32 channels x 4 rows.
-  // 256 -> 256 channels of 32-pixel rows: 8 x 64 rows 35 -> 34 us, 4 x 64 32 -> 25, 1 x 64
-  // 30 -> 19; 32 -> 32 of 512 x 256 11.5 -> 9.5.  A second round costs more than it gives: over
+  // 256 -> 256 channels of 32-pixel rows, full tiles against half of them: 8 x 64 rows 31.8
+  // and 29.4 us, 4 x 64 27.4 and 20.7; 1 x 64 27.1, 19.5 and, with 32 x 4 tiles, 14.3; 32 ->
+  // 32 of 512 x 256 11.5 and 8.8.  A second round costs more than it gives: over
   // 250 drawn sizes half tiles are 1.05 to 1.6 times as fast up to 512 of them and 0.79 to
   // 1.09 beyond (256 -> 128 of 4 x 59 x 224, 840 half tiles: 44 -> 52 us).  A pixel's sum
   // keeps its order.
