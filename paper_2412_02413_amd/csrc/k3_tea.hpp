@@ -266,11 +266,12 @@ __global__ __launch_bounds__(64 * TEA_WAVES) void k3_tea(TeaArgs a) {
 
 // Few elements: one thread a pixel makes its own phasors, with the delays in registers.  A row's table holds 4 PL phasors
 // however few pixels and elements the row has, so below some number of elements it costs more than it saves: of
-// 4 frames of 151 x 512 pixels and 205 bins, one element zero-stuffed takes 674 us with the table (12 phasors for each
-// one-pixel row) and 79 here, two 376 and 112, four 231 and 175; 3 frames of 317 x 384, 205 bins and six elements
-// zero-stuffed 303 and 184.  Timed both ways over 176 drawn calls of up to eight elements, this form is 1.05 to 1.65
-// times as fast where a depth's pixels times elements are at most 3.1 of its table phasors and 0.6 to 1.1 beyond 3.3
-// (calls above 30 us), so the line lies at 3.2; seven elements get there at most.
+// 4 frames of 151 x 512 pixels and 205 bins, one element zero-stuffed takes 672 us with the table (12 phasors for each
+// one-pixel row) and 77 here, two 375 and 99, four 232 and 144; padded (rows of 512 pixels in two tables of 264) two take
+// 129 and 99, three 134 and 120; 3 frames of 317 x 384, 205 bins and six elements zero-stuffed 303 and 184.  Timed both
+// ways over 176 drawn calls of up to eight elements, this form is 1.05 to 1.65 times as fast where a depth's pixels times
+// elements are at most 3.1 of its table phasors and 0.6 to 1.1 beyond 3.3 (calls above 30 us), so the line lies at 3.2;
+// seven elements get there at most.
 constexpr int kTeaFew = 7;
 inline bool tea_few(const TeaArgs& a) {              // (a's shape set)
   return a.L <= kTeaFew && 5ll * a.L * a.N <= 16ll * a.step * a.chunks * 4 * a.PL;
